@@ -899,6 +899,252 @@ __global__ __launch_bounds__(256) void head_reduce_kernel(const float* scratch, 
     __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Wide heads (C a multiple of 16, W past HEAD_WIDE_MIN elements): the same function as four launches
+// over the whole batch.  The per-sample kernel above reads all of W twice in every workgroup, so it
+// is bound by W's L2 traffic and one workgroup's serial sums over K (128 samples, 512 channels, 1000
+// classes: 312 + 37 us); here each product is a tiled contraction on fp32 MFMAs (products and sums
+// stay fp32) that reads W once per 16 samples (the same problem: pool 4.7, logits 7.4, softmax 4.8,
+// gradients 20 us, each now bound by its one or two rounds of loads).  scratch as above; z lives in the dlogits region until
+// the softmax replaces it.
+// ------------------------------------------------------------------------------------------------
+// one K step of 16 into four independent sums (element e of every chunk), which keeps each chain of
+// fp32 additions a quarter as long
+__device__ __forceinline__ void mma4(const Frag<float>& a, const Frag<float>& b, f32x4 (&acc)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[e], b.v[e], acc[e], 0, 0, 0);
+}
+
+// pooled[n][c]: 32 16-byte channel chunks x 8 pixel groups per workgroup
+template <typename T>
+__global__ __launch_bounds__(256) void head_pool_kernel(const void* yt, float* scratch, int HW, int C, int nsp) {
+  constexpr int VE = St<T>::VE;
+  __shared__ float part[8][32 * VE];
+  const int n = blockIdx.x / nsp, sp = blockIdx.x - n * nsp;
+  const int t = threadIdx.x, q = t & 31, g = t >> 5;
+  const int c0 = (sp * 32 + q) * VE;
+  float acc[VE];
+#pragma unroll
+  for (int v = 0; v < VE; ++v) acc[v] = 0.f;
+  if (c0 < C) {
+    const long base = (long)n * HW * C + c0;
+#pragma unroll 8
+    for (int h = g; h < HW; h += 8) {
+      Chunk<T> ch;
+      load_chunk<T>(yt, base + (long)h * C, ch);
+#pragma unroll
+      for (int v = 0; v < VE; ++v) acc[v] += ch.v[v];
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < VE; ++v) part[g][q * VE + v] = acc[v];
+  __syncthreads();
+  for (int i = t; i < 32 * VE; i += 256) {
+    const int c = sp * 32 * VE + i;
+    if (c >= C) break;
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += part[k][i];
+    scratch[(long)n * C + c] = s / (float)HW;
+  }
+}
+
+// z = pooled W^T + b: one 16 sample x 16 class tile per workgroup, its four waves a quarter of the
+// channel steps each (the partial tiles added in wave order)
+__global__ __launch_bounds__(256) void head_logits_kernel(const float* pooled, const float* eps, float* z,
+                                                          float* logits, int B, int C, int K, int tiles_k) {
+  __shared__ float red[4][16][17];
+  const int tn = blockIdx.x / tiles_k, tk = blockIdx.x - tn * tiles_k;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int r16 = lane & 15, grp = lane >> 4;
+  const float* a = pooled + (long)min(tn * 16 + r16, B - 1) * C + 4 * grp;
+  const float* b = eps + (long)min(tk * 16 + r16, K - 1) * C + 4 * grp;
+  f32x4 acc[4][4] = {};              // by step and element: chains of C / 256 additions of 4 products
+  const int steps = C / 16;
+  for (int s0 = wave; s0 < steps; s0 += 16) {
+    Frag<float> fa[4], fb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool on = s0 + 4 * u < steps;
+      fa[u].from_raw(*(const uint4*)(a + (on ? 16 * (s0 + 4 * u) : 0)));
+      fb[u].from_raw(*(const uint4*)(b + (on ? 16 * (s0 + 4 * u) : 0)));
+      if (!on) {
+        fa[u].zero();
+        fb[u].zero();
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) mma4(fa[u], fb[u], acc[u]);
+  }
+  f32x4 part[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) part[u] = (acc[u][0] + acc[u][1]) + (acc[u][2] + acc[u][3]);
+  const f32x4 sum = (part[0] + part[1]) + (part[2] + part[3]);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) red[wave][4 * grp + e][r16] = sum[e];
+  __syncthreads();
+  const int r = t >> 4, c = t & 15;
+  const int n = tn * 16 + r, k = tk * 16 + c;
+  if (n < B && k < K) {
+    const float v = ((red[0][r][c] + red[1][r][c]) + red[2][r][c]) + red[3][r][c] + eps[(long)K * C + k];
+    z[(long)n * K + k] = v;
+    if (logits) logits[(long)n * K + k] = v;
+  }
+}
+
+// per sample: log-sum-exp (exponentials summed in double), loss term, dlogits in place of z
+__global__ __launch_bounds__(256) void head_softmax_kernel(const int32_t* labels, float* zd, float* loss_n, int B,
+                                                           int K) {
+  extern __shared__ float sh[];   // z [K]
+  __shared__ float rm[4];
+  __shared__ double rs[4];
+  const int n = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  float* row = zd + (long)n * K;
+  float mx = -INFINITY;
+  for (int k = t; k < K; k += 256) {
+    const float v = row[k];
+    sh[k] = v;
+    mx = fmaxf(mx, v);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  if (lane == 0) rm[wave] = mx;
+  __syncthreads();
+  mx = fmaxf(fmaxf(rm[0], rm[1]), fmaxf(rm[2], rm[3]));
+  double se = 0.0;
+  for (int k = t; k < K; k += 256) se += exp((double)(sh[k] - mx));
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) se += __shfl_xor(se, o);
+  if (lane == 0) rs[wave] = se;
+  __syncthreads();
+  const float lse = mx + (float)log(((rs[0] + rs[1]) + rs[2]) + rs[3]);
+  const int lab = labels[n];
+  if (t == 0) loss_n[n] = lab >= 0 && lab < K ? lse - sh[lab] : NAN;   // a label outside [0, K): NaN loss
+  for (int k = t; k < K; k += 256) row[k] = (expf(sh[k] - lse) - (k == lab ? 1.f : 0.f)) / (float)B;
+}
+
+// Both gradients of the linear layer in one launch.  Workgroups [0, nD): D_N of 16 samples x 32
+// channels, dlogits W / HW stored over the pixels (sixteen waves: two 16-channel groups x eight
+// parts of the classes).  Workgroups [nD, ..): dW of 64 classes x 64 channels, dlogits^T pooled
+// (a 16 x 16 tile per wave); those of the first channel tile also db, the very first also the loss.
+template <typename T>
+__global__ __launch_bounds__(1024) void head_grad_kernel(const float* scratch, const float* eps, void* D_N,
+                                                         float* deps, float* loss, int B, int HW, int C, int K,
+                                                         int tiles_c, int nD, unsigned* flag) {
+  constexpr int VE = St<T>::VE, TC = 32;
+  __shared__ __attribute__((aligned(16))) float red[8][16][36];
+  const float* pooled = scratch;
+  const float* dlog = scratch + (long)B * C;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int r16 = lane & 15, grp = lane >> 4;
+  f32x4 acc[4] = {};
+  if ((int)blockIdx.x < nD) {
+    const int tiles_d = (C + TC - 1) / TC;
+    const int tn = blockIdx.x / tiles_d, tc = blockIdx.x - tn * tiles_d;
+    const int cg = wave & 1, ks = wave >> 1;
+    const int c = tc * TC + cg * 16 + r16;
+    const float* a = dlog + (long)min(tn * 16 + r16, B - 1) * K;
+    const float* w = eps + min(c, C - 1);
+    const int steps = (K + 15) / 16;
+#pragma unroll 8
+    for (int s = ks; s < steps; s += 8) {
+      Frag<float> fa, fb;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = 16 * s + 4 * grp + e, kc = min(k, K - 1);
+        const float v = a[kc], u = w[(long)kc * C];
+        fa.v[e] = k < K ? v : 0.f;
+        fb.v[e] = k < K ? u : 0.f;
+      }
+      mma4(fa, fb, acc);
+    }
+    const f32x4 sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[ks][4 * grp + e][cg * 16 + r16] = sum[e];
+    __syncthreads();
+    const int rr = (t & 511) >> 5, rc = t & 31;
+    float v = 0.f;
+    if (t < 512) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v += red[k][rr][rc];
+    }
+    __syncthreads();
+    if (t < 512) red[0][rr][rc] = v / (float)HW;
+    __syncthreads();
+    constexpr int CPP = TC / VE;                 // 16-byte chunks per pixel of the tile
+    const int q = t % CPP, c0 = tc * TC + q * VE;
+    if (c0 >= C) return;
+    const int items = min(16, B - tn * 16) * HW;
+    for (int i = t / CPP; i < items; i += 1024 / CPP) {
+      const int r = i / HW;
+      float d[VE];
+#pragma unroll
+      for (int v = 0; v < VE; v += 4) *(float4*)&d[v] = *(const float4*)&red[0][r][q * VE + v];
+      store_chunk<T>(D_N, ((long)tn * 16 * HW + i) * C + c0, d);
+    }
+    return;
+  }
+  const int b = blockIdx.x - nD;
+  const int tk = b / tiles_c, tc = b - tk * tiles_c;
+  const int k0 = tk * 64 + (wave & 3) * 16, c0 = tc * 64 + (wave >> 2) * 16;
+  bool bad = false;
+  {
+    const int kk = min(k0 + r16, K - 1), cc = min(c0 + r16, C - 1);
+#pragma unroll 8
+    for (int n0 = 0; n0 < B; n0 += 16) {
+      Frag<float> fa, fb;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int n = n0 + 4 * grp + e, nc = min(n, B - 1);
+        const float v = dlog[(long)nc * K + kk], u = pooled[(long)nc * C + cc];
+        fa.v[e] = n < B ? v : 0.f;
+        fb.v[e] = n < B ? u : 0.f;
+      }
+      mma4(fa, fb, acc);
+    }
+    const f32x4 sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    if (c0 + r16 < C)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = k0 + 4 * grp + e;
+        if (k < K) {
+          deps[(long)k * C + c0 + r16] = sum[e];
+          bad = bad || !isfinite(sum[e]);
+        }
+      }
+  }
+  if (tc == 0) {                                 // db: 64 classes x 16 sample lanes
+    const int kk = tk * 64 + (t & 63), l = t >> 6;
+    float s = 0.f;
+    if (kk < K)
+      for (int n = l; n < B; n += 16) s += dlog[(long)n * K + kk];
+    float* rb = &red[0][0][0];
+    rb[l * 64 + (t & 63)] = s;
+    __syncthreads();
+    if (t < 64 && kk < K) {
+      float v = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v += rb[i * 64 + t];
+      deps[(long)K * C + kk] = v;
+      bad = bad || !isfinite(v);
+    }
+  }
+  if (b == 0 && wave == 15) {
+    const float* ln = dlog + (long)B * K;
+    double sl = 0.0;
+    for (int n = lane; n < B; n += 64) sl += ln[n];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sl += __shfl_xor(sl, o);
+    if (lane == 0) {
+      const float v = (float)(sl / (double)B);
+      *loss = v;
+      bad = bad || !isfinite(v);
+    }
+  }
+  if (flag != nullptr && __syncthreads_or(bad) && t == 0)
+    __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __global__ void flags_clear_kernel(unsigned* flags) {
   if (threadIdx.x < PNN_NFLAGS) flags[threadIdx.x] = 0u;
 }
@@ -965,11 +1211,36 @@ int launch_sumsq(const float* part, int n, float* out, hipStream_t s) {
   return (int)hipGetLastError();
 }
 
+// W elements (K * C) from which the batch-tiled head is the faster one (per-sample / batch-tiled, us a
+// call: B 8, 20 x 64: 12.1 / 17.1; B 128, 10 x 256: 21.2 / 21.2; 64 x 64: 21.8 / 18.1; 100 x 256: 36.4 /
+// 19.8; 1000 x 512: 355 / 35.5; B 1, 1000 x 512: 277 / 18.9)
+constexpr long HEAD_WIDE_MIN = 4096;
+
 int launch_head(const void* yt, const float* eps, const int32_t* labels, float* logits, float* loss,
                 void* D_N, float* deps, float* scratch, int B, int HW, int C, int K, int dtype,
                 unsigned* flag, hipStream_t s) {
   const int es = dtype == 1 ? 2 : 4, ve = 16 / es;
   const bool vec = C % ve == 0 && ((uintptr_t)yt % 16) == 0 && ((uintptr_t)D_N % 16) == 0;
+  if (vec && C % 16 == 0 && (long)K * C >= HEAD_WIDE_MIN && ((uintptr_t)eps % 16) == 0 &&
+      ((uintptr_t)scratch % 16) == 0) {
+    float* z = scratch + (long)B * C;
+    const int nsp = (C / ve + 31) / 32, tiles_n = (B + 15) / 16, tiles_k = (K + 15) / 16, tiles_c = (C + 63) / 64;
+    const int nD = tiles_n * ((C + 31) / 32), nW = (K + 63) / 64 * tiles_c;
+    if (dtype == 1)
+      hipLaunchKernelGGL(head_pool_kernel<uint16_t>, dim3((unsigned)B * nsp), dim3(256), 0, s, yt, scratch, HW, C, nsp);
+    else
+      hipLaunchKernelGGL(head_pool_kernel<float>, dim3((unsigned)B * nsp), dim3(256), 0, s, yt, scratch, HW, C, nsp);
+    hipLaunchKernelGGL(head_logits_kernel, dim3((unsigned)tiles_n * tiles_k), dim3(256), 0, s, scratch, eps, z, logits,
+                       B, C, K, tiles_k);
+    hipLaunchKernelGGL(head_softmax_kernel, dim3(B), dim3(256), sizeof(float) * K, s, labels, z, z + (long)B * K, B, K);
+    if (dtype == 1)
+      hipLaunchKernelGGL(head_grad_kernel<uint16_t>, dim3(nD + nW), dim3(1024), 0, s, scratch, eps, D_N, deps, loss, B,
+                         HW, C, K, tiles_c, nD, flag);
+    else
+      hipLaunchKernelGGL(head_grad_kernel<float>, dim3(nD + nW), dim3(1024), 0, s, scratch, eps, D_N, deps, loss, B, HW,
+                         C, K, tiles_c, nD, flag);
+    return (int)hipGetLastError();
+  }
   int G = 0;
   if (vec) {
     const int nch = C / ve;
