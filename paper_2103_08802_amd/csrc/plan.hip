@@ -151,6 +151,24 @@ WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
   const int kc = es == 2 ? 256 : 128;               // stage rows of the halo kernel (W3Cfg::KC)
   const int ve = 16 / es;
   const long pq = (long)n.Ho * n.Wo;
+  // wide 3x3 bf16 problems: GEMM tiles of 128 (else 64) output
+  // channels x 128 (else 64) filter columns (one tap's channels), split over m in 64-pixel stages
+  // into about 512 workgroups (two per CU), at least 16 stages each
+  if (es == 2 && n.k == 3 && n.stride == 1 && n.pad == 1 && n.H == n.Ho && n.W == n.Wo && n.cin % 64 == 0 &&
+      n.cout % 64 == 0 && ((long)n.cin * n.cout >= 128 * 64 || M >= 32768) && M < (1L << 30)) {
+    WgradGeom g;
+    g.gemm = true;
+    g.wr = 0;
+    g.gtc = n.cout % 128 == 0 ? 128 : 64;
+    g.gtk = n.cin % 128 == 0 ? 128 : 64;
+    g.tiles_co = n.cout / g.gtc;
+    g.tiles_k = K / g.gtk;
+    const long base = (long)g.tiles_co * g.tiles_k;
+    const long splits = std::max(1L, std::min(cdiv(M, 16L * 64), cdiv(512, base)));
+    g.mchunk = (int)(cdiv(cdiv(M, splits), 64) * 64);
+    g.splits = (int)cdiv(M, g.mchunk);
+    return g;
+  }
   const bool whole_rows = kc % n.Wo == 0 && (pq % kc == 0 || kc % pq == 0);
   if (n.k == 3 && n.stride == 1 && n.pad == 1 && n.H == n.Ho && n.W == n.Wo && n.Wo % 8 == 0 &&
       n.cin % 16 == 0 && n.cout % 16 == 0 && whole_rows) {
@@ -168,24 +186,6 @@ WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
       g.splits = (int)cdiv(M, g.mchunk);
       return g;
     }
-  }
-  // wide 3x3 bf16 problems the halo kernel does not take: GEMM tiles of 128 (else 64) output
-  // channels x 128 (else 64) filter columns (one tap's channels), split over m in 64-pixel stages
-  // into about 512 workgroups (two per CU), at least 16 stages each
-  if (es == 2 && n.k == 3 && n.stride == 1 && n.pad == 1 && n.H == n.Ho && n.W == n.Wo && n.cin % 64 == 0 &&
-      n.cout % 64 == 0 && M < (1L << 30)) {
-    WgradGeom g;
-    g.gemm = true;
-    g.wr = 0;
-    g.gtc = n.cout % 128 == 0 ? 128 : 64;
-    g.gtk = n.cin % 128 == 0 ? 128 : 64;
-    g.tiles_co = n.cout / g.gtc;
-    g.tiles_k = K / g.gtk;
-    const long base = (long)g.tiles_co * g.tiles_k;
-    const long splits = std::max(1L, std::min(cdiv(M, 16L * 64), cdiv(512, base)));
-    g.mchunk = (int)(cdiv(cdiv(M, splits), 64) * 64);
-    g.splits = (int)cdiv(M, g.mchunk);
-    return g;
   }
   return wgrad_geom(n.cout, K, M);
 }
