@@ -67,14 +67,14 @@ def cpu_baseline(idx, batch=24, coarse="config"):
 # sources a kernel family's code and launch shapes come from; a stored traffic figure is void
 # once any of them changes
 KERNEL_SOURCES = {
-    "conv_kernel": ["k_conv.hip", "k_gemm.hip", "conv_epilogue.h", "bn_fuse.h", "device_common.h", "pnn_internal.h",
+    "conv_kernel": ["k_conv.hip", "k_gemm.hip", "k_hgemm.hip", "conv_epilogue.h", "bn_fuse.h", "device_common.h", "pnn_internal.h",
                     "plan.hip"],
     "wgrad_kernel": ["k_conv.hip", "device_common.h", "pnn_internal.h", "plan.hip"],
 }
 COPY_BYTES = 256 << 20          # the --copy-calibration copy
 # the kernels of a family: the launches the library's timing family covers (conv: every forward
 # and data-gradient convolution launch, the GEMM kernel's and its split-K reduce's included)
-FAMILY_KERNELS = {"conv_kernel": ("conv_kernel", "gemm_conv_kernel", "gemm_reduce_kernel")}
+FAMILY_KERNELS = {"conv_kernel": ("conv_kernel", "gemm_conv_kernel", "hgemm_conv_kernel", "gemm_reduce_kernel")}
 
 
 def _sources_sha(kernel):

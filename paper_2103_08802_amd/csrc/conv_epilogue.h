@@ -14,9 +14,15 @@ namespace pnn {
 // 16-byte column chunks of rows tid / ncc + k * rpp; pre / pre2 hold the streamed epilogue operands
 // of those chunks (loaded by the caller); piv_s is BNc floats of LDS for the forward pivot; bn is
 // [7][BNS] floats of LDS (mean, invstd, scale, shift; A, B, K) for the data-gradient BN forms.
-template <typename T, int MODE, int BM, int BNc, int LDA, int BNS>
+// rowm maps a tile row to its output pixel (TileRows: consecutive pixels).
+template <int BM>
+struct TileRows {
+  int tm;
+  __device__ __forceinline__ int operator()(int r) const { return tm * BM + r; }
+};
+template <typename T, int MODE, int BM, int BNc, int LDA, int BNS, typename RowMap>
 __device__ __forceinline__ void conv_epilogue(const ConvProb& P, float* acc_s, float* piv_s, const float* bn, int tm,
-                                              int n0, const uint4* pre, const uint4* pre2) {
+                                              int n0, const uint4* pre, const uint4* pre2, RowMap rowm) {
   constexpr int VE = St<T>::VE;
   constexpr int STAT_WORDS = 2 * 256 * VE + 512;
   constexpr int ACC_WORDS = BM * LDA > STAT_WORDS ? BM * LDA : STAT_WORDS;
@@ -53,7 +59,7 @@ __device__ __forceinline__ void conv_epilogue(const ConvProb& P, float* acc_s, f
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
     const int r = tid / ncc + k * rpp;
-    const int m = tm * BM + r;
+    const int m = rowm(r);
     if (m >= P.M) break;
     Chunk<T> pfc;
     unpack_chunk<T>(pre[k], pfc);
@@ -196,6 +202,12 @@ __device__ __forceinline__ void conv_epilogue(const ConvProb& P, float* acc_s, f
       bn_fwd_fuse((float2*)P.part, P.tiles_m, BM, (long)P.M, P.ncol, P.bn_gamma, P.bn_stats, P.bn_cnt, tm, n0 / BNc,
                   n0, BNc, (double*)acc_s);
   }
+}
+
+template <typename T, int MODE, int BM, int BNc, int LDA, int BNS>
+__device__ __forceinline__ void conv_epilogue(const ConvProb& P, float* acc_s, float* piv_s, const float* bn, int tm,
+                                              int n0, const uint4* pre, const uint4* pre2) {
+  conv_epilogue<T, MODE, BM, BNc, LDA, BNS>(P, acc_s, piv_s, bn, tm, n0, pre, pre2, TileRows<BM>{tm});
 }
 
 }  // namespace pnn

@@ -93,6 +93,8 @@ struct WgradGeom {
   bool halo3 = false;      // 3x3 / stride 1 / pad 1 through the halo kernel (tiles_k = Cg / 16)
   bool gemm = false;       // wide 3x3 / stride 1 / pad 1 bf16 through the GEMM kernel
   int gtc = 0, gtk = 0;    // its tile: output channels, filter columns (128 or 64)
+  bool row = false;        // without a prologue: the filter-row kernel (launch_wgrad_row), same splits
+  int uchunk = 0;          // its pixels per split, in rows padded by one column
 };
 
 }  // namespace
@@ -145,28 +147,43 @@ namespace {
 // would otherwise each walk hundreds of thousands of rows).
 WgradGeom wgrad_geom(int Co, int K, long M);
 
+// pixels from which a wide 3x3 bf16 weight gradient takes the filter-row kernel and, behind a BN, the
+// activation pass that goes with it (from 65536 / 16384 / 8192 / 4096 pixels, ms: the paper's coarse blocks
+// 3.27 / 3.20 / 3.12 / 3.11, CIFAR VGG-16 step 1.507 / 1.503 / 1.513 / 1.514, VGG layers at 224 px 12.30 /
+// 12.20 / - / 12.20); 128 x 128 tiles, at one wave per SIMD, ran at 547 TFLOP/s against 888 for 128 x 64
+constexpr long WGROW_MIN_M = 8192;
+
 WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
   const long M = (long)B * n.Ho * n.Wo;
   const int K = n.k * n.k * n.cin;
   const int kc = es == 2 ? 256 : 128;               // stage rows of the halo kernel (W3Cfg::KC)
   const int ve = 16 / es;
   const long pq = (long)n.Ho * n.Wo;
-  // wide 3x3 bf16 problems: GEMM tiles of 128 (else 64) output
-  // channels x 128 (else 64) filter columns (one tap's channels), split over m in 64-pixel stages
-  // into about 512 workgroups (two per CU), at least 16 stages each
+  // wide 3x3 bf16 problems: GEMM tiles of 128 (else 64) output channels x 128 (else 64) filter columns
+  // (one tap's channels), split over m in 64-pixel stages into about 512 workgroups (two per CU), at
+  // least 16 stages each.  64 x 64 channels only from 32768 pixels on: below, the halo kernel's larger
+  // grid is the faster (8192 pixels: coarse blocks 2.695 against 2.715 ms)
   if (es == 2 && n.k == 3 && n.stride == 1 && n.pad == 1 && n.H == n.Ho && n.W == n.Wo && n.cin % 64 == 0 &&
       n.cout % 64 == 0 && ((long)n.cin * n.cout >= 128 * 64 || M >= 32768) && M < (1L << 30)) {
     WgradGeom g;
     g.gemm = true;
     g.wr = 0;
     g.gtc = n.cout % 128 == 0 ? 128 : 64;
-    g.gtk = n.cin % 128 == 0 ? 128 : 64;
+    g.row = M >= WGROW_MIN_M;
+    g.gtk = n.cin % 128 == 0 && !(g.row && g.gtc == 128) ? 128 : 64;
     g.tiles_co = n.cout / g.gtc;
     g.tiles_k = K / g.gtk;
     const long base = (long)g.tiles_co * g.tiles_k;
-    const long splits = std::max(1L, std::min(cdiv(M, 16L * 64), cdiv(512, base)));
-    g.mchunk = (int)(cdiv(cdiv(M, splits), 64) * 64);
-    g.splits = (int)cdiv(M, g.mchunk);
+    long splits = std::max(1L, std::min(cdiv(M, 16L * 64), cdiv(512, base)));
+    if (g.row) {
+      // three taps per workgroup, two workgroups per CU
+      const long U = (long)B * n.Ho * (n.Wo + 1);
+      splits = std::max(1L, std::min(cdiv(U, 8L * 64), 512 / (base / 3)));
+      g.uchunk = (int)(cdiv(cdiv(U, splits), 64) * 64);
+      splits = cdiv(U, g.uchunk);
+    }
+    g.mchunk = (int)(cdiv(cdiv(M, splits), 64) * 64);   // (a split past the end stores zeros)
+    g.splits = (int)splits;
     return g;
   }
   const bool whole_rows = kc % n.Wo == 0 && (pq % kc == 0 || kc % pq == 0);
@@ -769,7 +786,10 @@ double conv_bytes(const ConvProb& p, int es, int mode) {
 int fire_conv_gk(const Ctx& c, std::vector<ConvProb>& probs, int mode, int gk, int wn, int wm) {
   pnn_plan* plan = c.plan;
   return grouped<ConvLaunch>(
-      probs, [](const ConvProb& p) { return p.tiles_m * p.tiles_n * std::max(p.ksplit, 1); },
+      probs,
+      [&](const ConvProb& p) {
+        return gk >= 6 ? (p.tiles_m + 1) / 2 * p.tiles_n : p.tiles_m * p.tiles_n * std::max(p.ksplit, 1);
+      },
       [&](const ConvLaunch& L, int tiles, size_t) {
         double fl = 0, by = 0;
         for (int i = 0; i < L.n; ++i) {
@@ -777,7 +797,8 @@ int fire_conv_gk(const Ctx& c, std::vector<ConvProb>& probs, int mode, int gk, i
           by += conv_bytes(L.p[i], plan->es, mode);
         }
         Timer t(plan, 1, c.stream);
-        int e = gk >= 4 ? launch_gemm(L, tiles, mode, gk == 5 ? 64 : GEMM_BN, c.stream)
+        int e = gk >= 6   ? launch_hgemm(L, tiles, mode, gk == 7 ? 64 : GEMM_BN, c.stream)
+                : gk >= 4 ? launch_gemm(L, tiles, mode, gk == 5 ? 64 : GEMM_BN, c.stream)
                         : launch_conv(L, tiles, plan->dtype, mode, gk, wn, wm, c.stream);
         t.done(c.stream, fl, by);
         return e;
@@ -818,25 +839,36 @@ int gemm_split(const ConvProb& q, long small) {
   return s >= 2 ? (int)s : 1;
 }
 
+// A GEMM problem (column tile tn) for the halo GEMM kernel: no prologue, tiles of consecutive pixels or
+// 16 x 16 patches, 32-bit byte offsets, and a 256-pixel tile per CU (two are resident: from 512 / 384 / 256 /
+// 128 tiles, VGG layers at 224 px 15.23 / 15.03 / 14.94 / 15.11 ms, at 96 px 0.502 / 0.502 / 0.494 / 0.499).
+constexpr long HG_MIN_TILES = 256;
+bool hgemm_ok(const ConvProb& p, int tn) {
+  return p.pro == nullptr && (p.Q <= HG_FLATW || (p.P % 16 == 0 && p.Q % 16 == 0)) &&
+         (long)p.M * p.Cg * 2 < (1L << 32) && (long)p.ncol * p.K * 2 < (1L << 31) && (long)p.M * p.ncol < (1L << 40) &&
+         cdiv(p.M, HG_BM) * (p.ncol / tn) >= HG_MIN_TILES;
+}
+
 // Gather kind of a convolution problem: 0 pointwise, 1 vector gather, 2 element-wise gather,
-// 3 halo tile, 4 the GEMM kernel with 128-column tiles, 5 with 64-column tiles.
+// 3 halo tile, 4 the GEMM kernel with 128-column tiles, 5 with 64-column tiles, 6 and 7 the halo
+// GEMM kernel likewise.
 int gather_kind(const ConvProb& p, int es) {
   if (p.Cg % (16 / es) != 0) return 2;
   if (p.k == 1 && p.stride == 1 && p.pad == 0) return 0;
   const int tn = gemm_tn(p, es);
-  if (tn != 0) return tn == GEMM_BN ? 4 : 5;
+  if (tn != 0) return (tn == GEMM_BN ? 4 : 5) + (hgemm_ok(p, tn) ? 2 : 0);
   if (halo_ok(p, es)) return 3;
   return 1;
 }
 
 // one grouped launch per (gather kind, column sub-tiles, tall / short tiles)
 int fire_conv(const Ctx& c, std::vector<ConvProb>& probs, int mode) {
-  std::vector<ConvProb> by[6][3][2];
+  std::vector<ConvProb> by[8][3][2];
   for (auto& p : probs) {
     const int w = p.wn == 1 ? 0 : p.wn == 2 ? 1 : 2;
     const int gk = gather_kind(p, c.plan->es);
     ConvProb q = p;
-    if (gk >= 4) q.tiles_n = q.ncol / (gk == 4 ? GEMM_BN : 64);
+    if (gk >= 4) q.tiles_n = q.ncol / (gk % 2 == 0 ? GEMM_BN : 64);
     by[gk][w][p.wm == conv_wm(p.wn, false) ? 0 : 1].push_back(q);
   }
   // GEMM launches: the longest K first, so that the longest tiles start first; the problems with
@@ -884,7 +916,7 @@ int fire_conv(const Ctx& c, std::vector<ConvProb>& probs, int mode) {
         koff += need;
         split.push_back(q);
       }
-  for (int gk = 0; gk < 6; ++gk)
+  for (int gk = 0; gk < 8; ++gk)
     for (int w = 0; w < 3; ++w)
       for (int t = 0; t < 2; ++t) {
         if (by[gk][w][t].empty()) continue;
@@ -977,21 +1009,27 @@ bool plan_splits_k(const pnn_plan* plan) {
   return false;
 }
 
-// A forward GEMM problem with a BN prologue whose input holds at least ACT_MIN_BYTES: its input is
-// activated once, ReLU(BN(z)) by the BN-ReLU pass into a per-chain region, and the GEMM reads that
+// A forward GEMM problem with a BN prologue that the halo GEMM kernel takes without one, or whose input
+// holds at least ACT_MIN_BYTES: its input is activated once, ReLU(BN(z)) by the BN-ReLU pass into a per-chain region, and the GEMM reads that
 // without a prologue.  The prologue would activate every input element once per tap and column
 // tile (9 x ncol / 128 times), which costs the forward GEMM a quarter of its MFMA rate on such
 // layers; the pass costs two tensor passes at the HBM rate.  Results are bit-identical (the same
 // fused multiply-add, ReLU and rounding).
 constexpr long ACT_MIN_BYTES = 32L << 20;
 bool act_materialize(const ConvProb& p, int es) {
-  return p.pro != nullptr && gemm_tn(p, es) != 0 && (long)p.B * p.H * p.W * p.Cg * es >= ACT_MIN_BYTES;
+  if (p.pro == nullptr) return false;
+  ConvProb q = p;
+  q.pro = nullptr;
+  const int tn = gemm_tn(q, es);
+  return tn != 0 && (hgemm_ok(q, tn) || (long)p.B * p.H * p.W * p.Cg * es >= ACT_MIN_BYTES);
 }
 
 // Likewise the input of a GEMM weight gradient with a BN prologue (the prologue there activates
-// each input element once per tap and output-channel tile).
+// each input element once per tap and output-channel tile); the filter-row kernel takes no other.
 bool wgrad_act(const NodeP& n, int B, int es) {
-  return n.bn >= 0 && wgrad_geom_node(n, B, es).gemm && (long)B * n.H * n.W * n.cin * es >= ACT_MIN_BYTES;
+  if (n.bn < 0) return false;
+  const WgradGeom g = wgrad_geom_node(n, B, es);
+  return g.row || (g.gemm && (long)B * n.H * n.W * n.cin * es >= ACT_MIN_BYTES);
 }
 
 // the forward geometry of conv node n (its prologue pointer only marked)
@@ -1340,7 +1378,7 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
   pnn_plan* plan = c.plan;
   const int B = plan->B, es = plan->es;
   char* wpart = c.wpart != nullptr ? c.wpart : c.scratch + plan->wpart_off;
-  std::vector<WgradProb> wg_vec, wg_gen, wg_h3, wg_pw, wg_gemm;
+  std::vector<WgradProb> wg_vec, wg_gen, wg_h3, wg_pw, wg_gemm, wg_row;
   std::vector<BnActProb> act;          // activated inputs of the GEMM weight gradients (wgrad_act)
   char* act_region = c.act != nullptr ? c.act : plan->act_stride != 0 ? c.scratch + plan->act_off : nullptr;
   size_t act_used = 0;
@@ -1390,7 +1428,9 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
       } else {
         const bool vec = n.cin % (16 / es) == 0;
         const bool pw = vec && n.k == 1 && n.stride == 1 && n.pad == 0;
-        (g.gemm ? wg_gemm : g.halo3 ? wg_h3 : pw ? wg_pw : vec ? wg_vec : wg_gen).push_back(p);
+        const bool row = g.row && p.pro == nullptr;   // (a full activation region leaves the prologue)
+        if (row) p.mchunk = g.uchunk;
+        (row ? wg_row : g.gemm ? wg_gemm : g.halo3 ? wg_h3 : pw ? wg_pw : vec ? wg_vec : wg_gen).push_back(p);
       }
       ColRedProb r;
       std::memset(&r, 0, sizeof(r));
@@ -1410,12 +1450,13 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
     if (e) return e;
   }
   // the GEMM problems by tile shape (one launch per shape)
-  std::vector<WgradProb> wg_gemm_by[4];
+  std::vector<WgradProb> wg_gemm_by[8];   // (4 ..: the filter-row kernel)
   for (const WgradProb& p : wg_gemm) wg_gemm_by[(p.gtc == 128 ? 0 : 2) + (p.gtk == 128 ? 0 : 1)].push_back(p);
-  for (int v = 0; v < 8; ++v) {
+  for (const WgradProb& p : wg_row) wg_gemm_by[4 + (p.gtc == 128 ? 0 : 2) + (p.gtk == 128 ? 0 : 1)].push_back(p);
+  for (int v = 0; v < 12; ++v) {
     auto& list = v == 0 ? wg_vec : v == 1 ? wg_gen : v == 2 ? wg_h3 : v == 3 ? wg_pw : wg_gemm_by[v - 4];
     int e = grouped<WgradLaunch>(
-        list, [](const WgradProb& p) { return p.tiles_co * p.tiles_k * p.splits; },
+        list, [v](const WgradProb& p) { return p.tiles_co * p.tiles_k / (v >= 8 ? 3 : 1) * p.splits; },
         [&](const WgradLaunch& Lx, int tiles, size_t) {
           double fl = 0, by = 0;
           for (int i = 0; i < Lx.n; ++i) {
@@ -1425,6 +1466,7 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
           }
           Timer t(plan, 2, c.stream);
           int e2 = v == 2   ? launch_wgrad3(Lx, tiles, plan->dtype, c.stream)
+                   : v >= 8 ? launch_wgrad_row(Lx, tiles, Lx.p[0].gtc, Lx.p[0].gtk, c.stream)
                    : v >= 4 ? launch_wgrad_gemm(Lx, tiles, Lx.p[0].gtc, Lx.p[0].gtk, c.stream)
                             : launch_wgrad(Lx, tiles, plan->dtype, v == 0 ? WG_VEC : v == 1 ? WG_GEN : WG_PW,
                                            c.stream);

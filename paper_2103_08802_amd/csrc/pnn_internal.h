@@ -324,6 +324,12 @@ int launch_conv(const ConvLaunch& L, int tiles, int dtype, int mode, int gk, int
 constexpr int GEMM_BM = 128, GEMM_BN = 128, GEMM_BK = 64;
 constexpr int CONV_PRO_MAXC = 512;     // largest Cg of a forward BN prologue held in LDS
 int launch_gemm(const ConvLaunch& L, int tiles, int mode, int tn, hipStream_t s);   // tn: 128 or 64
+// large wide 3x3 problems without a prologue (k_hgemm.hip): HG_BM output pixels x tn columns per
+// workgroup, the input pixels of a 64-channel chunk staged once for all taps; bit-identical to launch_gemm
+constexpr int HG_BM = 256;
+constexpr int HG_AROWS = 376;                   // input pixels staged per workgroup, at most (a multiple of 8)
+constexpr int HG_FLATW = (HG_AROWS - HG_BM - 2) / 2;   // widest map whose flat halo (W + 1 on both sides) fits
+int launch_hgemm(const ConvLaunch& L, int tiles, int mode, int tn, hipStream_t s);   // tn: 128 or 64
 // the split problems' second pass: partial tiles summed in split order, then the epilogue, one
 // workgroup per GEMM_RBN-column slab of a tile
 int launch_gemm_reduce(const ConvLaunch& L, int tiles, int mode, hipStream_t s);
@@ -342,6 +348,9 @@ int launch_wgrad(const WgradLaunch& L, int tiles, int dtype, int gather, hipStre
 // wide 3x3 / stride 1 / pad 1 bf16 weight gradients (C_in, C_out multiples of 128) as 128 x 128 GEMM
 // tiles over the pixels (k_gemm.hip); tiles_co = C_out / 128, tiles_k = 9 C_in / 128
 int launch_wgrad_gemm(const WgradLaunch& L, int tiles, int tc, int tk, hipStream_t s);   // tc, tk: 128 or 64
+// large ones without a prologue, one filter row (three taps) per workgroup (k_hgemm.hip): tiles_co x tiles_k / 3
+// workgroups per split; mchunk in pixels of rows padded by one column, a multiple of 64
+int launch_wgrad_row(const WgradLaunch& L, int tiles, int tc, int tk, hipStream_t s);   // 128 x 64, 64 x 128, 64 x 64
 // Streaming pointwise convolution of narrow problems (1x1 / stride 1 / pad 0, ncol % 32 != 0,
 // K <= PW_MAXK): FWD with an optional BN prologue and EPI_STATS (no residual or addend); BWD with
 // EPI_BN_MASK.  16-column workgroup tiles; wm = tiles of PW_TR rows per workgroup;
