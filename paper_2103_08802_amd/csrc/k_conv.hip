@@ -31,94 +31,78 @@ namespace pnn {
 // ------------------------------------------------------------------------------------------------
 enum { GK_POINT = 0, GK_VEC = 1, GK_SCALAR = 2, GK_HALO = 3 };
 
+// The stored 16-byte chunk of A at row (m; pixel n, p, q) and K position k0 (GK_POINT, GK_VEC), without a
+// branch: where A is zero (ok = false: padding, rows past M, columns past K) the tensor's first chunk.
+// c0: the chunk's first channel.
 template <typename T, int MODE, int GK>
-__device__ __forceinline__ void gather_a(const ConvProb& P, const float2* pro, int m, int n, int p, int q,
-                                         bool rowok, int k0, Frag<T>& a) {
-  constexpr int VE = St<T>::VE;
-  const bool prologue = MODE == MODE_FWD && P.pro != nullptr;
+__device__ __forceinline__ uint4 gather_raw(const ConvProb& P, int m, int n, int p, int q, bool rowok, int k0, bool& ok,
+                                            int& c0) {
+  ok = rowok && k0 < P.K;
+  long idx;
   if constexpr (GK == GK_POINT) {
-    if (!(rowok && k0 < P.K)) {
-      a.zero();
-      return;
-    }
-    const long idx = (long)m * P.Cg + k0;
-    if (prologue) {
-      Chunk<T> c;
-      load_chunk<T>(P.in, idx, c);
-#pragma unroll
-      for (int e = 0; e < VE; ++e) c.v[e] = fmaxf(fmaf(c.v[e], pro[k0 + e].x, pro[k0 + e].y), 0.0f);
-      a.from_chunk(c);
-    } else {
-      a.from_raw(*(const uint4*)((const T*)P.in + idx));
-    }
-  } else if constexpr (GK == GK_VEC) {
+    c0 = k0;
+    idx = (long)m * P.Cg + k0;
+  } else {
     const int tap = div_l2(k0, P.Cg, P.cg_log2);
-    const int c0 = k0 - tap * P.Cg;
+    c0 = k0 - tap * P.Cg;
     int r, s;
     tap_rs(tap, P.k, r, s);
     int ih, iw;
-    bool ok = rowok && k0 < P.K;
     if constexpr (MODE == MODE_FWD) {
       ih = p * P.stride + r - P.pad;
       iw = q * P.stride + s - P.pad;
     } else {
       const int th = p + P.pad - r, tw = q + P.pad - s;
-      if (P.stride == 1) {
-        ih = th;
-        iw = tw;
-      } else {   // stride 2
+      ih = th;
+      iw = tw;
+      if (P.stride != 1) {   // stride 2
         ok = ok && th >= 0 && tw >= 0 && ((th | tw) & 1) == 0;
         ih = th >> 1;
         iw = tw >> 1;
       }
     }
     ok = ok && (unsigned)ih < (unsigned)P.H && (unsigned)iw < (unsigned)P.W;
-    if (!ok) {
-      a.zero();
-      return;
-    }
-    const long idx = (((long)n * P.H + ih) * P.W + iw) * P.Cg + c0;
-    if (prologue) {
-      Chunk<T> c;
-      load_chunk<T>(P.in, idx, c);
-#pragma unroll
-      for (int e = 0; e < VE; ++e) c.v[e] = fmaxf(fmaf(c.v[e], pro[c0 + e].x, pro[c0 + e].y), 0.0f);
-      a.from_chunk(c);
-    } else {
-      a.from_raw(*(const uint4*)((const T*)P.in + idx));
-    }
-  } else {
-    Chunk<T> c;
-#pragma unroll
-    for (int e = 0; e < VE; ++e) {
-      const int kk = k0 + e;
-      float v = 0.0f;
-      if (rowok && kk < P.K) {
-        const int tap = kk / P.Cg;
-        const int ch = kk - tap * P.Cg;
-        const int r = tap / P.k;
-        const int s = tap - r * P.k;
-        int ih, iw;
-        bool ok = true;
-        if constexpr (MODE == MODE_FWD) {
-          ih = p * P.stride + r - P.pad;
-          iw = q * P.stride + s - P.pad;
-        } else {
-          const int th = p + P.pad - r, tw = q + P.pad - s;
-          ok = th >= 0 && tw >= 0 && (th % P.stride) == 0 && (tw % P.stride) == 0;
-          ih = th / P.stride;
-          iw = tw / P.stride;
-        }
-        ok = ok && (unsigned)ih < (unsigned)P.H && (unsigned)iw < (unsigned)P.W;
-        if (ok) {
-          v = St<T>::ld(P.in, (((long)n * P.H + ih) * P.W + iw) * P.Cg + ch);
-          if (prologue) v = fmaxf(fmaf(v, pro[ch].x, pro[ch].y), 0.0f);
-        }
-      }
-      c.v[e] = v;
-    }
-    a.from_chunk(c);
+    idx = (((long)n * P.H + ih) * P.W + iw) * P.Cg + c0;
   }
+  return *(const uint4*)((const T*)P.in + (ok ? idx : 0));
+}
+
+// GK_SCALAR: the chunk element by element, prologue applied
+template <typename T, int MODE>
+__device__ __forceinline__ void gather_scalar(const ConvProb& P, const float2* pro, int n, int p, int q, bool rowok,
+                                              int k0, Frag<T>& a) {
+  constexpr int VE = St<T>::VE;
+  const bool prologue = MODE == MODE_FWD && P.pro != nullptr;
+  Chunk<T> c;
+#pragma unroll
+  for (int e = 0; e < VE; ++e) {
+    const int kk = k0 + e;
+    float v = 0.0f;
+    if (rowok && kk < P.K) {
+      const int tap = kk / P.Cg;
+      const int ch = kk - tap * P.Cg;
+      const int r = tap / P.k;
+      const int s = tap - r * P.k;
+      int ih, iw;
+      bool ok = true;
+      if constexpr (MODE == MODE_FWD) {
+        ih = p * P.stride + r - P.pad;
+        iw = q * P.stride + s - P.pad;
+      } else {
+        const int th = p + P.pad - r, tw = q + P.pad - s;
+        ok = th >= 0 && tw >= 0 && (th % P.stride) == 0 && (tw % P.stride) == 0;
+        ih = th / P.stride;
+        iw = tw / P.stride;
+      }
+      ok = ok && (unsigned)ih < (unsigned)P.H && (unsigned)iw < (unsigned)P.W;
+      if (ok) {
+        v = St<T>::ld(P.in, (((long)n * P.H + ih) * P.W + iw) * P.Cg + ch);
+        if (prologue) v = fmaxf(fmaf(v, pro[ch].x, pro[ch].y), 0.0f);
+      }
+    }
+    c.v[e] = v;
+  }
+  a.from_chunk(c);
 }
 
 template <typename T, bool VEC>
@@ -416,17 +400,94 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvLaunch L) {
   }
 
   if constexpr (GK == GK_HALO) conv_halo<T, MODE, WM, WN>(P, pro_s, (T*)acc_s, tm, n0, acc, load_epi);
-  for (int kk = kstart; kk < P.K && GK != GK_HALO; kk += KS) {
-    const int k0 = kk + VE * grp;
-    Frag<T> a[WM];
+  if constexpr (GK == GK_SCALAR) {
+    for (int kk = 0; kk < P.K; kk += KS) {
+      const int k0 = kk + VE * grp;
+      Frag<T> a[WM];
 #pragma unroll
-    for (int wm = 0; wm < WM; ++wm) gather_a<T, MODE, GK>(P, pro_s, rm[wm], rn[wm], rp[wm], rq[wm], rv[wm], k0, a[wm]);
+      for (int wm = 0; wm < WM; ++wm) gather_scalar<T, MODE>(P, pro_s, rn[wm], rp[wm], rq[wm], rv[wm], k0, a[wm]);
 #pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      Frag<T> b;
-      load_b<T, GK != GK_SCALAR>(P, n0 + j * 16 + r16, k0, b);
+      for (int j = 0; j < WN; ++j) {
+        Frag<T> b;
+        load_b<T, false>(P, n0 + j * 16 + r16, k0, b);
 #pragma unroll
-      for (int wm = 0; wm < WM; ++wm) mma(a[wm], b, acc[wm][j]);
+        for (int wm = 0; wm < WM; ++wm) mma(a[wm], b, acc[wm][j]);
+      }
+    }
+  } else if constexpr (GK != GK_HALO) {
+    // fp32 and short tiles only: in the tall bf16 tiles the second set costs more in resident waves than it
+    // hides (ResNet-1001 step 13.97 ms with it, 13.49 without; 64 px units 1.75 and 1.65 ms)
+    constexpr bool PIPE = WM * WN < CONV_SUBTILES || sizeof(T) == 4;
+    // PIPE, two register sets: a step's loads are in flight while the step before is multiplied (each step's
+    // loads and their wait in turn took a load latency per step: fp32 units 876 -> 762 us, coarse blocks
+    // 2.70 -> 2.61 ms)
+    struct Step {
+      uint4 a[WM], b[WN];
+      unsigned ok;                 // bit wm: row wm's chunk is part of A
+      int c0;
+      bool bok;
+    };
+    auto load = [&](int kk, Step& S) {
+      const int k0 = kk + VE * grp;
+      S.ok = 0;
+#pragma unroll
+      for (int wm = 0; wm < WM; ++wm) {
+        bool ok;
+        S.a[wm] = gather_raw<T, MODE, GK>(P, rm[wm], rn[wm], rp[wm], rq[wm], rv[wm], k0, ok, S.c0);
+        S.ok |= ok ? 1u << wm : 0u;
+      }
+      S.bok = k0 < P.K;
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+        S.b[j] = *(const uint4*)((const T*)P.wmat + (S.bok ? (long)(n0 + j * 16 + r16) * P.K + k0 : 0));
+    };
+    auto use = [&](const Step& S) {
+      Frag<T> a[WM];
+      const bool prologue = MODE == MODE_FWD && P.pro != nullptr;
+      float2 ps[VE];
+      if (prologue) {
+        const int c0 = S.ok ? S.c0 : 0;          // (columns past K: any constants, the operand is zero)
+#pragma unroll
+        for (int e = 0; e < VE; ++e) ps[e] = pro_s[c0 + e];
+      }
+#pragma unroll
+      for (int wm = 0; wm < WM; ++wm) {
+        if (prologue) {
+          Chunk<T> c;
+          unpack_chunk<T>(S.a[wm], c);
+#pragma unroll
+          for (int e = 0; e < VE; ++e) c.v[e] = fmaxf(fmaf(c.v[e], ps[e].x, ps[e].y), 0.0f);
+          a[wm].from_chunk(c);
+        } else {
+          a[wm].from_raw(S.a[wm]);
+        }
+        if (!((S.ok >> wm) & 1u)) a[wm].zero();
+      }
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        Frag<T> b;
+        b.from_raw(S.b[j]);
+        if (!S.bok) b.zero();
+#pragma unroll
+        for (int wm = 0; wm < WM; ++wm) mma(a[wm], b, acc[wm][j]);
+      }
+    };
+    if constexpr (PIPE) {
+      Step S0, S1;
+      if (kstart < P.K) load(kstart, S0);
+      for (int kk = kstart; kk < P.K; kk += 2 * KS) {
+        if (kk + KS < P.K) load(kk + KS, S1);
+        use(S0);
+        if (kk + KS >= P.K) break;
+        if (kk + 2 * KS < P.K) load(kk + 2 * KS, S0);
+        use(S1);
+      }
+    } else {
+      for (int kk = kstart; kk < P.K; kk += KS) {
+        Step S;
+        load(kk, S);
+        use(S);
+      }
     }
   }
 
