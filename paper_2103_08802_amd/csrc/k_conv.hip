@@ -23,13 +23,16 @@ namespace pnn {
 //                   GK_HALO   3x3 / stride 1 / pad 1 (forward, and its data gradient, which is the
 //                             same stencil with the taps mirrored): the tile's input rows plus a
 //                             one-pixel halo are staged in LDS once, the filter column of each wave
-//                             is held in registers, and every K step reads A from LDS.
+//                             is held in registers, and every K step reads A from LDS,
+//                   GK_FLAT   the same on maps whose rows do not divide the tile, and in fp32: the tile's
+//                             pixels and W + 1 more on both sides, consecutive in memory, in LDS; padding
+//                             taps read a row of zeros.
 // The BN prologue's (scale, shift) and the data-gradient epilogue's BN statistics are staged in LDS
 // once per workgroup.  The epilogue stages the fp32 tile through LDS so that every thread owns
 // 16-byte column chunks: residual / mask-source loads and output stores are 16-byte vectors, and
 // each thread's BN partial sums cover fixed columns (combined in a fixed order).
 // ------------------------------------------------------------------------------------------------
-enum { GK_POINT = 0, GK_VEC = 1, GK_SCALAR = 2, GK_HALO = 3 };
+enum { GK_POINT = 0, GK_VEC = 1, GK_SCALAR = 2, GK_HALO = 3, GK_FLAT = 4 };
 
 // The stored 16-byte chunk of A at row (m; pixel n, p, q) and K position k0 (GK_POINT, GK_VEC), without a
 // branch: where A is zero (ok = false: padding, rows past M, columns past K) the tensor's first chunk.
@@ -257,6 +260,110 @@ __device__ __forceinline__ void conv_halo(const ConvProb& P, const float2* pro, 
   __syncthreads();                            // the halo region is reused by the epilogue
 }
 
+// GK_FLAT main loop.  The tile's BM output pixels are consecutive in the flat (image, row, column) index,
+// whatever the map's width; LDS holds input pixels m0 - W - 1 .. m0 + BM + W (one linear copy, BN prologue
+// applied on the way), a pixel's chunks at an odd chunk stride where that fits (16 lanes reading one chunk
+// of 16 consecutive pixels then meet all banks once), and after them a row of zeros that the taps outside
+// the image read.  Filter fragments in registers and sub-tile ownership as in conv_halo.
+template <typename T, int MODE, int WM, int WN, typename F>
+__device__ __forceinline__ void conv_flat(const ConvProb& P, const float2* pro, T* rows, int tm, int n0,
+                                          f32x4 (&acc)[WM][WN], F&& before_compute) {
+  constexpr int VE = St<T>::VE;
+  constexpr int KS = 4 * VE;
+  constexpr int BM = 64 * WM;
+  constexpr int NKB = conv_flat_nkb(sizeof(T));
+  constexpr int NL = 8;
+  const int tid = threadIdx.x;
+  const int wave = tid >> 6, lane = tid & 63;
+  const int r16 = lane & 15, grp = lane >> 4;
+  const int W = P.Q, PQ = P.P * P.Q;
+  const int cpp = P.Cg / VE;
+  const int PS = conv_flat_stride(cpp, BM, W) * VE;
+  const int R = BM + 2 * W + 2;
+  const int total = R * cpp;
+  const int m0 = tm * BM;
+  const int nsteps = (P.K + KS - 1) / KS;
+
+  Frag<T> bq[NKB];
+#pragma unroll
+  for (int s = 0; s < NKB; ++s) {
+    if (s < nsteps) load_b<T, true>(P, n0 + r16, s * KS + VE * grp, bq[s]);
+    else bq[s].zero();
+  }
+
+  const float r_cpp = 1.0f / cpp;
+  const long first = ((long)m0 - W - 1) * cpp, last = (long)P.M * cpp - 1;   // chunks
+  for (int base = 0; base < total; base += 256 * NL) {
+    uint4 v[NL];
+#pragma unroll
+    for (int u = 0; u < NL; ++u)
+      v[u] = *(const uint4*)((const T*)P.in + min(max(first + base + u * 256 + tid, 0L), last) * VE);
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int idx = base + u * 256 + tid;
+      if (idx >= total) continue;
+      int pix, ch;
+      divmod_small(idx, cpp, r_cpp, pix, ch);
+      uint4 w = v[u];
+      if (MODE == MODE_FWD && P.pro != nullptr) {
+        Chunk<T> c;
+        unpack_chunk<T>(w, c);
+        float f[VE];
+#pragma unroll
+        for (int e = 0; e < VE; ++e) f[e] = fmaxf(fmaf(c.v[e], pro[ch * VE + e].x, pro[ch * VE + e].y), 0.0f);
+        store_chunk<T>(&w, 0, f);
+      }
+      *(uint4*)(rows + pix * PS + ch * VE) = w;
+    }
+  }
+  if (tid < cpp) *(uint4*)(rows + R * PS + tid * VE) = make_uint4(0, 0, 0, 0);
+
+  int rb[WM];                                  // LDS element offset of the sub-tile row's pixel
+  unsigned mk[WM];                             // its taps inside the image
+#pragma unroll
+  for (int t = 0; t < WM; ++t) {
+    const int lm = (wave * WM + t) * 16 + r16;
+    const int m = m0 + lm;
+    const bool v = m < P.M;
+    const int mm = v ? m : 0;
+    const int n = div_l2(mm, PQ, P.pq_log2);
+    const int rem = mm - n * PQ;
+    const int p = div_l2(rem, W, P.q_log2);
+    const int q = rem - p * W;
+    rb[t] = (lm + W + 1) * PS;
+    unsigned k = 0;
+#pragma unroll
+    for (int u = 0; u < 9; ++u) {
+      const int dr = MODE == MODE_FWD ? u / 3 - 1 : 1 - u / 3;
+      const int dq = MODE == MODE_FWD ? u % 3 - 1 : 1 - u % 3;
+      k |= (v && (unsigned)(p + dr) < (unsigned)P.H && (unsigned)(q + dq) < (unsigned)W) ? 1u << u : 0u;
+    }
+    mk[t] = k;
+  }
+  __syncthreads();
+  before_compute();                           // the epilogue's early loads overlap the K loop
+
+#pragma unroll
+  for (int s = 0; s < NKB; ++s) {
+    if (s < nsteps) {
+      int k0 = s * KS + VE * grp;
+      if (k0 >= P.K) k0 = 0;                  // (the filter fragment there is zero)
+      const int tap = div_l2(k0, P.Cg, P.cg_log2);
+      const int c0 = k0 - tap * P.Cg;
+      int r, q;
+      tap_rs(tap, 3, r, q);
+      const int toff = ((MODE == MODE_FWD) ? ((r - 1) * W + q - 1) : ((1 - r) * W + 1 - q)) * PS + c0;
+#pragma unroll
+      for (int t = 0; t < WM; ++t) {
+        Frag<T> a;
+        a.from_raw(*(const uint4*)(rows + (((mk[t] >> tap) & 1u) ? rb[t] + toff : R * PS)));
+        mma(a, bq[s], acc[t][0]);
+      }
+    }
+  }
+  __syncthreads();                            // the rows' region is reused by the epilogue
+}
+
 // WM row sub-tiles of 16 per wave, WN column sub-tiles: a workgroup owns a (64 WM) x (16 WN) tile
 // (tall tiles: WM * WN = CONV_SUBTILES, so narrow problems get taller tiles; short tiles: 2 or 4).
 template <typename T, int MODE, int GK, int WM, int WN>
@@ -267,7 +374,9 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvLaunch L) {
   constexpr int LDA = 16 * WN + 4;
   constexpr int STAT_WORDS = 2 * 256 * VE + 512;   // BN sums reduce (epilogue)
   constexpr int ACC_WORDS0 = BM * LDA > STAT_WORDS ? BM * LDA : STAT_WORDS;
-  constexpr int ACC_WORDS = (GK == GK_HALO && CONV_HALO_BYTES / 4 > ACC_WORDS0) ? CONV_HALO_BYTES / 4 : ACC_WORDS0;
+  constexpr bool LDSA = GK == GK_HALO || GK == GK_FLAT;   // A through LDS
+  constexpr int IN_WORDS = GK == GK_HALO ? CONV_HALO_BYTES / 4 : GK == GK_FLAT ? CONV_FLAT_BYTES / 4 : 0;
+  constexpr int ACC_WORDS = IN_WORDS > ACC_WORDS0 ? IN_WORDS : ACC_WORDS0;
   // BN prologue constants (forward only) and BN statistics / apply coefficients (data gradient
   // only): each mode allocates only its own, which keeps four workgroups resident per CU
   __shared__ float2 pro_s[MODE == MODE_FWD ? CONV_PRO_MAXC : 1];
@@ -293,7 +402,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvLaunch L) {
   int rm[WM], rn[WM], rp[WM], rq[WM];
   bool rv[WM];
 #pragma unroll
-  for (int wm = 0; wm < WM && GK != GK_HALO; ++wm) {
+  for (int wm = 0; wm < WM && !LDSA; ++wm) {
     const int m = mw + wm * 16 + r16;
     rv[wm] = m < P.M;
     const int mm = rv[wm] ? m : 0;
@@ -339,7 +448,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvLaunch L) {
       pre2[k] = (pf2 != nullptr && m < P.M) ? *(const uint4*)((const T*)pf2 + o) : make_uint4(0, 0, 0, 0);
     }
   };
-  if constexpr (GK != GK_HALO) load_epi();
+  if constexpr (!LDSA) load_epi();
   // K steps whose operands are loaded before the barrier: two for the tall 16-column tiles
   // (their 1x1 problems have K = 64 = two steps), one otherwise
   constexpr int ES = (GK == GK_POINT && WM >= 8) ? 2 : 1;
@@ -400,6 +509,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvLaunch L) {
   }
 
   if constexpr (GK == GK_HALO) conv_halo<T, MODE, WM, WN>(P, pro_s, (T*)acc_s, tm, n0, acc, load_epi);
+  if constexpr (GK == GK_FLAT) conv_flat<T, MODE, WM>(P, pro_s, (T*)acc_s, tm, n0, acc, load_epi);
   if constexpr (GK == GK_SCALAR) {
     for (int kk = 0; kk < P.K; kk += KS) {
       const int k0 = kk + VE * grp;
@@ -414,7 +524,7 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvLaunch L) {
         for (int wm = 0; wm < WM; ++wm) mma(a[wm], b, acc[wm][j]);
       }
     }
-  } else if constexpr (GK != GK_HALO) {
+  } else if constexpr (!LDSA) {
     // fp32 and short tiles only: in the tall bf16 tiles the second set costs more in resident waves than it
     // hides (ResNet-1001 step 13.97 ms with it, 13.49 without; 64 px units 1.75 and 1.65 ms)
     constexpr bool PIPE = WM * WN < CONV_SUBTILES || sizeof(T) == 4;
@@ -496,9 +606,9 @@ __global__ __launch_bounds__(256) void conv_kernel(const ConvLaunch L) {
   for (int wm = 0; wm < WM; ++wm)
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
-      // row / column sub-tile of acc[wm][j]: waves split rows, or (GK_HALO) columns first
-      const int rt = (GK == GK_HALO) ? (wave / WN) * (WM * WN) + wm * WN + j : wave * WM + wm;
-      const int ct = (GK == GK_HALO) ? wave % WN : j;
+      // row / column sub-tile of acc[wm][j]: waves split rows, or (A through LDS) columns first
+      const int rt = LDSA ? (wave / WN) * (WM * WN) + wm * WN + j : wave * WM + wm;
+      const int ct = LDSA ? wave % WN : j;
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc_s[(rt * 16 + grp * 4 + i) * LDA + ct * 16 + r16] = acc[wm][j][i];
     }
@@ -1507,6 +1617,9 @@ static void launch_conv_v(const ConvLaunch& L, int tiles, int gk, hipStream_t s)
     hipLaunchKernelGGL((conv_kernel<T, MODE, GK_VEC, WM, WN>), dim3(tiles), dim3(256), 0, s, L);
   else if (gk == GK_HALO)
     hipLaunchKernelGGL((conv_kernel<T, MODE, GK_HALO, WM, WN>), dim3(tiles), dim3(256), 0, s, L);
+  else if (gk == GK_FLAT) {
+    if constexpr (WN == 1) hipLaunchKernelGGL((conv_kernel<T, MODE, GK_FLAT, WM, 1>), dim3(tiles), dim3(256), 0, s, L);
+  }
   else
     hipLaunchKernelGGL((conv_kernel<T, MODE, GK_SCALAR, WM, WN>), dim3(tiles), dim3(256), 0, s, L);
 }

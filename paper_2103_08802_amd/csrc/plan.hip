@@ -788,7 +788,7 @@ int fire_conv_gk(const Ctx& c, std::vector<ConvProb>& probs, int mode, int gk, i
   return grouped<ConvLaunch>(
       probs,
       [&](const ConvProb& p) {
-        return gk >= 6 ? (p.tiles_m + 1) / 2 * p.tiles_n : p.tiles_m * p.tiles_n * std::max(p.ksplit, 1);
+        return gk == 6 || gk == 7 ? (p.tiles_m + 1) / 2 * p.tiles_n : p.tiles_m * p.tiles_n * std::max(p.ksplit, 1);
       },
       [&](const ConvLaunch& L, int tiles, size_t) {
         double fl = 0, by = 0;
@@ -797,7 +797,8 @@ int fire_conv_gk(const Ctx& c, std::vector<ConvProb>& probs, int mode, int gk, i
           by += conv_bytes(L.p[i], plan->es, mode);
         }
         Timer t(plan, 1, c.stream);
-        int e = gk >= 6   ? launch_hgemm(L, tiles, mode, gk == 7 ? 64 : GEMM_BN, c.stream)
+        int e = gk == 8   ? launch_conv(L, tiles, plan->dtype, mode, 4, wn, wm, c.stream)
+                : gk >= 6 ? launch_hgemm(L, tiles, mode, gk == 7 ? 64 : GEMM_BN, c.stream)
                 : gk >= 4 ? launch_gemm(L, tiles, mode, gk == 5 ? 64 : GEMM_BN, c.stream)
                         : launch_conv(L, tiles, plan->dtype, mode, gk, wn, wm, c.stream);
         t.done(c.stream, fl, by);
@@ -818,6 +819,15 @@ bool halo_ok(const ConvProb& p, int es) {
   const long rows = bm > pq ? p.P : bm / p.Q;
   const long ps = p.Cg + (long)conv_halo_pad(p.Cg / ve, p.Q) * ve;
   return nimg * (rows + 2) * (p.Q + 2) * ps * es <= CONV_HALO_BYTES;
+}
+
+// A 3x3 / stride 1 / pad 1 problem with 16-column tiles for the flat tiles: its pixels fit CONV_FLAT_BYTES, its
+// filter the registers
+bool flat_ok(const ConvProb& p, int es) {
+  if (p.k != 3 || p.stride != 1 || p.pad != 1 || p.H != p.P || p.W != p.Q) return false;
+  const int ve = 16 / es, bm = 64 * p.wm;
+  return p.wn == 1 && p.Cg % ve == 0 && p.K <= 4 * ve * conv_flat_nkb(es) && p.Q < (1 << 16) &&
+         conv_flat_stride(p.Cg / ve, bm, p.Q) > 0;
 }
 
 // A 3x3 / stride 1 / pad 1 bf16 problem for the GEMM kernel: K steps of GEMM_BK channels within
@@ -851,24 +861,24 @@ bool hgemm_ok(const ConvProb& p, int tn) {
 
 // Gather kind of a convolution problem: 0 pointwise, 1 vector gather, 2 element-wise gather,
 // 3 halo tile, 4 the GEMM kernel with 128-column tiles, 5 with 64-column tiles, 6 and 7 the halo
-// GEMM kernel likewise.
+// GEMM kernel likewise, 8 flat tiles.
 int gather_kind(const ConvProb& p, int es) {
   if (p.Cg % (16 / es) != 0) return 2;
   if (p.k == 1 && p.stride == 1 && p.pad == 0) return 0;
   const int tn = gemm_tn(p, es);
   if (tn != 0) return (tn == GEMM_BN ? 4 : 5) + (hgemm_ok(p, tn) ? 2 : 0);
   if (halo_ok(p, es)) return 3;
-  return 1;
+  return flat_ok(p, es) ? 8 : 1;
 }
 
 // one grouped launch per (gather kind, column sub-tiles, tall / short tiles)
 int fire_conv(const Ctx& c, std::vector<ConvProb>& probs, int mode) {
-  std::vector<ConvProb> by[8][3][2];
+  std::vector<ConvProb> by[9][3][2];
   for (auto& p : probs) {
     const int w = p.wn == 1 ? 0 : p.wn == 2 ? 1 : 2;
     const int gk = gather_kind(p, c.plan->es);
     ConvProb q = p;
-    if (gk >= 4) q.tiles_n = q.ncol / (gk % 2 == 0 ? GEMM_BN : 64);
+    if (gk >= 4 && gk < 8) q.tiles_n = q.ncol / (gk % 2 == 0 ? GEMM_BN : 64);
     by[gk][w][p.wm == conv_wm(p.wn, false) ? 0 : 1].push_back(q);
   }
   // GEMM launches: the longest K first, so that the longest tiles start first; the problems with
@@ -916,7 +926,7 @@ int fire_conv(const Ctx& c, std::vector<ConvProb>& probs, int mode) {
         koff += need;
         split.push_back(q);
       }
-  for (int gk = 0; gk < 8; ++gk)
+  for (int gk = 0; gk < 9; ++gk)
     for (int w = 0; w < 3; ++w)
       for (int t = 0; t < 2; ++t) {
         if (by[gk][w][t].empty()) continue;

@@ -310,7 +310,7 @@ int launch_unit_fwd(const UnitLaunch& L, hipStream_t s);
 int unit_fwd_occupancy();    // workgroups of the resident kernel that fit the device at once
 
 // gk: 0 = pointwise (1x1, stride 1, pad 0), 1 = vector gather, 2 = element-wise gather,
-//     3 = 3x3 / stride 1 / pad 1 through an LDS halo tile;
+//     3 = 3x3 / stride 1 / pad 1 through an LDS halo tile, 4 = the same as flat pixels;
 // wn: 16-column sub-tiles per wave (1, 2, 4) shared by every problem of the launch
 // every launch record fits the 4 KB of kernel arguments
 static_assert(sizeof(ConvLaunch) <= 4096 && sizeof(WgradLaunch) <= 4096 && sizeof(ColRedLaunch) <= 4096 &&
@@ -413,12 +413,16 @@ inline int conv_bm(int ncol) { return 64 * (CONV_SUBTILES / conv_wn(ncol)); }
 // tall tiles give): 2 sub-tiles per wave for 16- and 32-column tiles, 4 for 64-column tiles
 inline int conv_wm(int wn, bool short_tiles) { return short_tiles ? (wn == 1 ? 2 : 1) : CONV_SUBTILES / wn; }
 constexpr int SHORT_TILES_BELOW = 512;   // workgroups of a tall tiling below which short tiles pay
+constexpr int SHORT3_TILES_BELOW = 32;   // ... of a 3x3 problem, whatever its segment (fp32 network, 8 tall
+                                         // tiles: 264 us a step, 32 short ones: 176)
 // row sub-tiles per wave of a k x k convolution problem with M rows and ncol columns in a segment
-// that allows short tiles: short for 1x1 problems with few tall tiles (3x3 keep tall tiles)
+// that allows short tiles: short for 1x1 problems with few tall tiles (3x3: below)
 inline int conv_rows_wm(int k, long M, int ncol, bool short_ok) {
   const int wn = conv_wn(ncol), tall = CONV_SUBTILES / wn;
-  if (!short_ok || k != 1) return tall;
   const long tiles = (M + 64 * tall - 1) / (64 * tall) * (ncol / (16 * wn));
+  // a 3x3 problem of a few tall tiles runs at one tile's latency (64-column problems keep the GEMM's rows)
+  if (k == 3 && wn < 4 && tiles < SHORT3_TILES_BELOW) return conv_wm(wn, true);
+  if (!short_ok || k != 1) return tall;
   return tiles < SHORT_TILES_BELOW ? conv_wm(wn, true) : tall;
 }
 constexpr int ELT_TILE = 2048;     // elements per workgroup of elementwise kernels
@@ -444,10 +448,18 @@ constexpr int CONV_HALO_BYTES = 40960;  // LDS of a 3x3 halo tile (input rows + 
 // K steps whose filter fragments a wave keeps in registers, by column sub-tiles per wave (the
 // register budget of narrow tiles, which carry more row sub-tiles, is smaller)
 __host__ __device__ constexpr int conv_halo_nkb(int wn) { return wn == 1 ? 5 : wn == 2 ? 9 : 18; }
+// the same of a flat tile (16 columns; K steps of 64 bytes of channels)
+__host__ __device__ constexpr int conv_flat_nkb(int es) { return es == 2 ? 5 : 9; }
 // unused 16-byte chunks after the cpp channel chunks of a halo pixel (output width Q): two for
 // pixels of four or more chunks, a pixel stride of 8 dwords modulo 16 (measured: 8-wide maps with
 // 64 channels took 4.3 LDS conflict cycles per LDS-active cycle with one chunk, 2.4 with two)
 __host__ __device__ inline int conv_halo_pad(int cpp, int Q) { return cpp >= 4 ? 2 : 0; }
-
+// flat 3x3 tiles (GK_FLAT): LDS of the staged pixels and the row of zeros, and the chunks from one pixel
+// to the next: odd where that fits, else the cpp of the pixel (-1: neither fits)
+constexpr int CONV_FLAT_BYTES = 49152;
+__host__ __device__ inline int conv_flat_stride(int cpp, int bm, int W) {
+  const int rows = bm + 2 * W + 3, odd = cpp | 1;
+  return rows * odd * 16 <= CONV_FLAT_BYTES ? odd : rows * cpp * 16 <= CONV_FLAT_BYTES ? cpp : -1;
+}
 
 }  // namespace pnn
