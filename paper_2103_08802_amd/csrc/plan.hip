@@ -1698,6 +1698,13 @@ int run_bwd(const Ctx& c, const std::vector<const SegP*>& segs, const std::vecto
 // is enqueued before level L + 1, and the small launches of one group overlap the others'.  One
 // fork (the side streams wait for the call's stream) and one join (the call's stream waits for
 // them) per call.  Timed runs keep one stream.
+//
+// A call whose sub-networks keep less than CHAIN_MIN_BYTES stays on the call's stream: there the fork, the
+// join and the host's four times as many launches cost more than the overlap saves.  One / four streams, us:
+// fp32 network (0.4 MB) 177 / 283, ResNet units of 9 MB 408 / 561, of 30 MB 375 / 388, of 150 MB 915 / 865,
+// of 300 MB 1914 / 1651.  Plans with K-split GEMM problems (VGG) keep their chains: how such a problem is split,
+// and with it the order of its sums, depends on the problems it shares a call with.
+constexpr size_t CHAIN_MIN_BYTES = (size_t)40 << 20;
 struct Chains {
   std::vector<std::vector<const SegP*>> segs;
   std::vector<std::vector<Ptrs>> ptrs;
@@ -1709,7 +1716,10 @@ struct Chains {
 int chains_group(const Ctx& c, const std::vector<const SegP*>& segs, const std::vector<Ptrs>& ptrs,
                  Chains& ch) {
   pnn_plan* p = c.plan;
-  const int maxg = p->timing_family != 0 ? 1 : std::min(p->streams, (int)p->side.size() + 1);
+  size_t saved = 0;
+  for (auto* sp : segs) saved += sp->saved_bytes;
+  const bool few = saved < CHAIN_MIN_BYTES && p->kpart_stride == 0;
+  const int maxg = p->timing_family != 0 || few ? 1 : std::min(p->streams, (int)p->side.size() + 1);
   std::vector<long> keys;
   for (size_t i = 0; i < segs.size(); ++i) {
     const long key = (long)segs[i]->slots[0].H << 20 | segs[i]->slots[0].W;   // the stage
