@@ -645,13 +645,45 @@ __global__ __launch_bounds__(256) void transpose_kernel(const TransposeLaunch L)
   const int o0 = (rest % tiles_o) * 64, c0 = (rest / tiles_o) * 64;
   const T* w = (const T*)P.w;
   T* wt = (T*)P.wt;
-  for (int k = threadIdx.x; k < 64 * 64; k += 256) {
-    const int r = k >> 6, cc = k & 63;       // read w[o0 + r][tp][c0 + cc]
+  // a launch is a few workgroups long and runs at one tile's latency: every load of the tile is in flight
+  // at once, in 16-byte chunks (element loads in turn took 10 us a launch, this 5)
+  constexpr int VE = St<T>::VE, CPR = 64 / VE, NC = 64 * CPR / 256;
+  const int tid = threadIdx.x;
+  if (P.C % VE == 0 && P.O % VE == 0) {
+    uint4 v[NC];
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {             // read w[o0 + r][tp][c0 + cc ..]
+      const int r = (tid + 256 * u) / CPR, cc = (tid + 256 * u) % CPR * VE;
+      const bool ok = o0 + r < P.O && c0 + cc < P.C;
+      v[u] = *(const uint4*)(w + (ok ? ((long)(o0 + r) * P.T + tp) * P.C + c0 + cc : 0));
+    }
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      const int r = (tid + 256 * u) / CPR, cc = (tid + 256 * u) % CPR * VE;
+      const T* e = (const T*)&v[u];
+#pragma unroll
+      for (int k = 0; k < VE; ++k) tile[r][cc + k] = e[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {             // write wt[c0 + r][tp][o0 + oo ..]
+      const int r = (tid + 256 * u) / CPR, oo = (tid + 256 * u) % CPR * VE;
+      if (c0 + r >= P.C || o0 + oo >= P.O) continue;
+      uint4 x;
+      T* e = (T*)&x;
+#pragma unroll
+      for (int k = 0; k < VE; ++k) e[k] = tile[oo + k][r];
+      *(uint4*)(wt + ((long)(c0 + r) * P.T + tp) * P.O + o0 + oo) = x;
+    }
+    return;
+  }
+  for (int k = tid; k < 64 * 64; k += 256) {
+    const int r = k >> 6, cc = k & 63;         // read w[o0 + r][tp][c0 + cc]
     if (o0 + r < P.O && c0 + cc < P.C) tile[r][cc] = w[((long)(o0 + r) * P.T + tp) * P.C + c0 + cc];
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < 64 * 64; k += 256) {
-    const int r = k >> 6, oo = k & 63;       // write wt[c0 + r][tp][o0 + oo]
+  for (int k = tid; k < 64 * 64; k += 256) {
+    const int r = k >> 6, oo = k & 63;         // write wt[c0 + r][tp][o0 + oo]
     if (c0 + r < P.C && o0 + oo < P.O) wt[((long)(c0 + r) * P.T + tp) * P.O + o0 + oo] = tile[oo][r];
   }
 }
