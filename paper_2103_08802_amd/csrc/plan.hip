@@ -33,6 +33,7 @@ struct NodeP {
   size_t w_off = NONE, gw_off = NONE, wt_off = NONE;
   bool dgrad = false;      // data gradient needed in the backward
   bool first_of_two = false;
+  bool alone = false;      // its launches hold one problem (a coarse block's)
   bool resident = false;   // part of the segment's run of resident units (unit_fwd_kernel)
 };
 
@@ -145,13 +146,26 @@ namespace {
 // workgroup, split-K in multiples of the stage.  Everything else: (16 wr) x 64 dW tiles, split-K
 // over m in multiples of 128 rows into about 1024 workgroups (four per CU: a wide layer's few tiles
 // would otherwise each walk hundreds of thousands of rows).
-WgradGeom wgrad_geom(int Co, int K, long M);
+WgradGeom wgrad_geom(const NodeP& n, long M, int es);
 
 // pixels from which a wide 3x3 bf16 weight gradient takes the filter-row kernel and, behind a BN, the
 // activation pass that goes with it (from 65536 / 16384 / 8192 / 4096 pixels, ms: the paper's coarse blocks
 // 3.27 / 3.20 / 3.12 / 3.11, CIFAR VGG-16 step 1.507 / 1.503 / 1.513 / 1.514, VGG layers at 224 px 12.30 /
 // 12.20 / - / 12.20); 128 x 128 tiles, at one wave per SIMD, ran at 547 TFLOP/s against 888 for 128 x 64
 constexpr long WGROW_MIN_M = 8192;
+
+// Stages per split of the halo weight gradient and rows per split of the general one.  A launch with fewer
+// workgroups than CUs runs at one split's latency, so splits are shorter where a launch holds one problem
+// (coarse blocks, `alone`: 2.51 -> 2.31 ms), in fp32 (units 756 -> 720 us) and in problems of under 32
+// workgroups (fp32 network 174 -> 145 us); elsewhere the sub-networks' other problems fill the launch and shorter
+// splits only add partial rows (ResNet-1001 step 13.5 -> 13.7 ms at half, 13.9 to 14.2 at a quarter).
+struct WgradRows {
+  long usual, alone, f32, few;
+};
+constexpr WgradRows W3_STAGES{4, 2, 2, 1}, WG_ROWS{512, 128, 256, 128};
+long wgrad_rows(const WgradRows& r, const NodeP& n, long wg, int es) {   // wg: workgroups at the usual split
+  return wg < 32 ? r.few : wg < 300 && n.alone ? r.alone : wg < 300 && es == 4 ? r.f32 : r.usual;
+}
 
 WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
   const long M = (long)B * n.Ho * n.Wo;
@@ -198,22 +212,25 @@ WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
       g.tiles_co = n.cout / 16;
       g.tiles_k = n.cin / 16;
       const long base = (long)g.tiles_co * g.tiles_k;
-      long splits = std::max(1L, std::min(cdiv(M, 4L * kc), cdiv(256, base)));
+      const long stages = wgrad_rows(W3_STAGES, n, base * cdiv(M, W3_STAGES.usual * kc), es);
+      long splits = std::max(1L, std::min(cdiv(M, stages * kc), cdiv(256, base)));
       g.mchunk = (int)(cdiv(cdiv(M, splits), kc) * kc);
       g.splits = (int)cdiv(M, g.mchunk);
       return g;
     }
   }
-  return wgrad_geom(n.cout, K, M);
+  return wgrad_geom(n, M, es);
 }
 
-WgradGeom wgrad_geom(int Co, int K, long M) {
+WgradGeom wgrad_geom(const NodeP& n, long M, int es) {
+  const int Co = n.cout, K = n.k * n.k * n.cin;
   WgradGeom g;
   g.wr = (Co % 64 == 0) ? 4 : (Co % 32 == 0) ? 2 : 1;
   g.tiles_co = Co / (16 * g.wr);
   g.tiles_k = (int)cdiv(K, 64);
   const long base = (long)g.tiles_co * g.tiles_k;
-  long splits = std::max(1L, std::min(cdiv(M, 512), cdiv(1024, base)));
+  const long rows = wgrad_rows(WG_ROWS, n, base * cdiv(M, WG_ROWS.usual), es);
+  long splits = std::max(1L, std::min(cdiv(M, rows), cdiv(1024, base)));
   long mchunk = cdiv(cdiv(M, splits), 128) * 128;
   g.mchunk = (int)mchunk;
   g.splits = (int)cdiv(M, mchunk);
@@ -300,6 +317,7 @@ pnn_status build_segment(const pnn_segment_desc& d, int part, int index, int B, 
     NodeP n;
     n.op = x.op; n.src = x.src; n.dst = x.dst; n.bn = x.bn; n.pool = x.pool; n.k = x.k;
     n.stride = x.stride; n.pad = x.pad; n.cout = x.cout; n.res = x.res;
+    n.alone = S.short_tiles;
     if (n.src < 0 || n.src >= n_slots || !made[n.src]) return PNN_ERR_SHAPE;
     if (n.dst <= 0 || n.dst >= n_slots || made[n.dst]) return PNN_ERR_SHAPE;
     if (n.res >= n_slots || (n.res >= 0 && !made[n.res])) return PNN_ERR_SHAPE;
