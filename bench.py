@@ -74,7 +74,7 @@ KERNEL_SOURCES = {
 COPY_BYTES = 256 << 20          # the --copy-calibration copy
 # the kernels of a family: the launches the library's timing family covers (conv: every forward
 # and data-gradient convolution launch, the GEMM kernel's and its split-K reduce's included)
-FAMILY_KERNELS = {"conv_kernel": ("conv_kernel", "gemm_conv_kernel", "hgemm_conv_kernel", "gemm_reduce_kernel")}
+FAMILY_KERNELS = {"conv_kernel": ("conv_kernel", "gemm_conv_kernel", "hgemm_conv_kernel", "sgemm_conv_kernel", "gemm_reduce_kernel")}
 
 
 def _sources_sha(kernel):

@@ -293,6 +293,216 @@ int launch_hgemm(const ConvLaunch& L, int tiles, int mode, int tn, hipStream_t s
 }
 
 // ------------------------------------------------------------------------------------------------
+// Short halo GEMM: the same convolution (and its data gradient) where 256-pixel tiles would leave CUs idle.
+// 128 pixels x 64 output channels per workgroup, four waves of 32 x 64; maps of at most SG_FLATW columns.
+//
+// Such a launch is one workgroup per CU and runs at that workgroup's latency: gemm_conv_kernel's 128 x 128 tiles
+// (half of the CUs at 8 x 8 pixels x 256 channels, batch 128) wait for their loads and a barrier in each of
+// the 9 Cg / 64 steps, and its forward forms the BN prologue once per tap.  Here the filter rows run two steps
+// ahead in three buffers, and the next chunk's input rows arrive during the current chunk's taps, one
+// 16-byte load per lane and step, so no step waits for a load issued in the one before.  A BN prologue is
+// applied in place, once per chunk: a wave activates the rows that it loaded itself two steps earlier.
+//
+// K runs as in gemm_conv_kernel (chunk outer, tap inner): results are bit-identical to its unsplit ones.
+// Measured (the paper's coarse blocks, batch 128, 9.7 GFLOP a launch; gemm_conv_kernel before): 256 channels at
+// 8 x 8 pixels, 256 workgroups, forward 50.0 -> 28.2 us, data gradient 39.8 -> 23.5; 128 channels at 16 x 16, 512
+// workgroups, 32.9 -> 22.2 and 26.4 -> 18.1 us (343 to 534 TFLOP/s).
+// ------------------------------------------------------------------------------------------------
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void sgemm_conv_kernel(const ConvLaunch L) {
+  using T = uint16_t;
+  constexpr int VE = 8, TN = 64, BM = 128;
+  constexpr int A_BYTES = SG_AROWS * HROW;            // one input buffer
+  constexpr int B_BYTES = TN * HROW;                  // one filter buffer
+  constexpr int ZERO = 2 * A_BYTES;                   // the row of zeros
+  constexpr int B0 = ZERO + HROW;
+  constexpr int LDA = TN + 4;
+  constexpr int SMEM = B0 + 3 * B_BYTES;
+  static_assert(BM * LDA * 4 + 8 * TN * 4 <= SMEM, "the epilogue's tile, BN constants and pivot");
+  static_assert(2 * (SMEM + CONV_PRO_MAXC * 8) <= 160 * 1024, "two workgroups per CU");
+  static_assert(SG_AROWS % 8 == 0 && (SG_AROWS / 8 + 3) / 4 <= 7, "a wave's pieces are activated by tap 8");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
+  __shared__ __attribute__((aligned(16))) float2 pro_s[CONV_PRO_MAXC];
+
+  const int gi = find_group(L);
+  const ConvProb& P = L.p[gi];
+  const int local = blockIdx.x - P.tile_begin;
+  // the column tiles of a row tile on one XCD, as in hgemm_conv_kernel
+  const int per = P.tiles_m / 8;
+  int tm, tn;
+  if (local < 8 * per * P.tiles_n) {
+    const int q = local >> 3;
+    tm = (local & 7) * per + q / P.tiles_n;
+    tn = q % P.tiles_n;
+  } else {
+    const int l2 = local - 8 * per * P.tiles_n;
+    tm = 8 * per + l2 / P.tiles_n;
+    tn = l2 % P.tiles_n;
+  }
+  const int n0 = tn * TN, m0 = tm * BM;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int r32 = lane & 31, kh = lane >> 5;
+  const int W = P.Q, H = P.P, PQ = H * W;
+  const bool prologue = MODE == MODE_FWD && P.pro != nullptr;
+
+  // input loads: piece j of the wave fills rows 8 (wave + 4 j) .. + 7 (pixels clamped to the tensor: a clamped
+  // row is no tap's, its output pixel being outside or at the image's edge)
+  const int lrow = lane >> 3, lch = (lane & 7) ^ lrow;
+  const int R = BM + 2 * W + 2;
+  const int nai = (R + 31 - 8 * wave) / 32;
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  const uint32_t boff = (uint32_t)(((long)(n0 + 8 * wave + lrow) * P.K + 8 * lch) * 2);
+  const uint32_t bstep = (uint32_t)(32L * P.K * 2);
+  const char* in = (const char*)P.in;
+  const char* wm = (const char*)P.wmat;
+  const int nchunk = P.Cg / 64, total = 9 * nchunk;
+  auto load_a = [&](int cb, int j) {
+    const long pix = min(max((long)m0 - W - 1 + 8 * (wave + 4 * j) + lrow, 0L), (long)P.M - 1);
+    load_lds16(lds0 + (cb & 1) * A_BYTES + (wave + 4 * j) * 1024, in + cb * HROW, (uint32_t)((pix * P.Cg + 8 * lch) * 2));
+  };
+  auto load_b = [&](int cb, int tap, int buf) {
+    const char* base = wm + ((long)tap * P.Cg + cb * 64) * 2;
+#pragma unroll
+    for (int j = 0; j < TN / 32; ++j)
+      load_lds16(lds0 + B0 + buf * B_BYTES + (wave + 4 * j) * 1024, base, boff + j * bstep);
+  };
+  // piece j of chunk cb, loaded by this lane: ReLU(x scale + shift) of its 8 channels
+  auto activate = [&](int cb, int j) {
+    uint4* at = (uint4*)(smem + (cb & 1) * A_BYTES + (wave + 4 * j) * 1024 + 16 * lane);
+    Chunk<T> v;
+    unpack_chunk<T>(*at, v);
+    const float2* ps = pro_s + cb * 64 + 8 * lch;
+    float f[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) f[e] = fmaxf(fmaf(v.v[e], ps[e].x, ps[e].y), 0.0f);
+    uint4 w;
+    store_chunk<T>(&w, 0, f);
+    *at = w;
+  };
+
+  // the lane's fragment row: LDS row of the output pixel itself and the taps inside the image
+  const int lm = wave * 32 + r32, arow = lm + W + 1;
+  unsigned amask = 0;
+  {
+    const int m = m0 + lm;
+    const bool v = m < P.M;
+    const int mm = v ? m : 0;
+    const int rem = mm - div_l2(mm, PQ, P.pq_log2) * PQ;
+    const int p = div_l2(rem, W, P.q_log2);
+    const int q = rem - p * W;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int dr = MODE == MODE_FWD ? t / 3 - 1 : 1 - t / 3;
+      const int dq = MODE == MODE_FWD ? t % 3 - 1 : 1 - t % 3;
+      amask |= (v && (unsigned)(p + dr) < (unsigned)H && (unsigned)(q + dq) < (unsigned)W) ? 1u << t : 0u;
+    }
+  }
+  uint32_t bfr[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) bfr[kk] = B0 + r32 * HROW + ((32 * kk + 16 * kh) ^ ((r32 & 7) << 4));
+
+  f32x16 acc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+
+  if (tid < HROW / 4) *(float*)(smem + ZERO + 4 * tid) = 0.f;
+  if (prologue)
+    for (int c = tid; c < P.Cg; c += 256) pro_s[c] = make_float2(P.pro[c], P.pro[P.Cg + c]);
+  for (int j = 0; j < nai; ++j) load_a(0, j);
+  load_b(0, 0, 0);
+  load_b(0, 1, 1);
+  if (prologue) {
+    // all but the second filter tap has landed; the constants are in LDS
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    for (int j = 0; j < nai; ++j) activate(0, j);
+  }
+  int buf = 0, s = 0;
+  bool piece = false;                                 // an input piece was issued in the step before
+  for (int cb = 0; cb < nchunk; ++cb) {
+    const bool more = cb + 1 < nchunk;
+#pragma unroll 1
+    for (int tap = 0; tap < 9; ++tap, ++s) {
+      // Issued since this step's filter rows (two steps ago, after that step's input piece): the step before's
+      // piece and the next step's filter rows.  All else has landed, in every wave, and every wave is past the
+      // step before, whose filter buffer (and, at tap 0, input buffer) is free.
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + 1 >= total) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else if (piece) asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      piece = more && tap < nai;
+      if (piece) load_a(cb + 1, tap);
+      const int b2 = buf == 0 ? 2 : buf - 1;          // (buf + 2) % 3
+      if (tap < 7) load_b(cb, tap + 2, b2);
+      else if (more) load_b(cb + 1, tap - 7, b2);
+      if (prologue && more && tap >= 2 && tap - 2 < nai) activate(cb + 1, tap - 2);
+      const int dr = MODE == MODE_FWD ? tap / 3 - 1 : 1 - tap / 3;
+      const int dq = MODE == MODE_FWD ? tap % 3 - 1 : 1 - tap % 3;
+      const int rr = arow + dr * W + dq;
+      const uint32_t ab = ((amask >> tap) & 1u) ? (cb & 1) * A_BYTES + rr * HROW : ZERO;
+      const uint32_t ax = ((rr & 7) << 4) ^ (16 * kh);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const bf16x8 a = *(const bf16x8*)(smem + (ab + ((32 * kk) ^ ax)));
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const bf16x8 b = *(const bf16x8*)(smem + buf * B_BYTES + bfr[kk] + 32 * j * HROW);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+        }
+      }
+      buf = buf == 2 ? 0 : buf + 1;
+    }
+  }
+  lds_ready();                                        // every wave is past its last fragments
+
+  float* accs = (float*)smem;
+  float* bn_s = accs + BM * LDA;
+  float* piv = bn_s + 7 * TN;
+  const bool bnmask = MODE == MODE_BWD && (P.flags & (EPI_BN_MASK | EPI_BN_APPLY));
+  constexpr int ncc = TN / VE, rpp = 256 / ncc, NCH = BM / rpp;
+  const int cc0 = (tid % ncc) * VE;
+  const void* pf = (MODE == MODE_FWD) ? P.res
+                   : ((P.flags & EPI_STORE_F32) ? nullptr : (bnmask ? P.zsrc : P.res));
+  const void* pf2 = (MODE == MODE_FWD) ? P.ext : ((P.flags & EPI_BN_APPLY) ? P.res : nullptr);
+  if (bnmask && tid < TN) {
+    const int col = n0 + tid;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bn_s[k * TN + tid] = P.bnst[k * P.ncol + col];
+    if (P.flags & EPI_BN_APPLY) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) bn_s[(4 + k) * TN + tid] = P.coef[k * P.ncol + col];
+    }
+  }
+  uint4 pre[NCH], pre2[NCH];
+#pragma unroll
+  for (int k = 0; k < NCH; ++k) {
+    const int m = m0 + tid / ncc + k * rpp;
+    const long o = (long)m * P.ncol + n0 + cc0;
+    pre[k] = (pf != nullptr && m < P.M) ? *(const uint4*)((const T*)pf + o) : make_uint4(0, 0, 0, 0);
+    pre2[k] = (pf2 != nullptr && m < P.M) ? *(const uint4*)((const T*)pf2 + o) : make_uint4(0, 0, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      accs[(wave * 32 + 8 * (e >> 2) + 4 * kh + (e & 3)) * LDA + 32 * j + r32] = acc[j][e];
+  __syncthreads();
+  conv_epilogue<T, MODE, BM, TN, LDA, TN>(P, accs, piv, bn_s, tm, n0, pre, pre2);
+}
+
+int launch_sgemm(const ConvLaunch& L, int tiles, int mode, hipStream_t s) {
+  if (mode == MODE_FWD)
+    hipLaunchKernelGGL((sgemm_conv_kernel<MODE_FWD>), dim3(tiles), dim3(256), 0, s, L);
+  else
+    hipLaunchKernelGGL((sgemm_conv_kernel<MODE_BWD>), dim3(tiles), dim3(256), 0, s, L);
+  return (int)hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
 // Weight gradient of a large wide 3x3 / stride 1 / pad 1 bf16 convolution without a BN prologue:
 // dW[co][(r, s, c)] = sum over pixels of g[pixel][co] in[pixel + (r - 1, s - 1)][c], TC output channels x TK
 // input channels x the three taps of one filter row per workgroup, split over the pixels.

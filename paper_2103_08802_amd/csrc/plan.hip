@@ -816,6 +816,7 @@ int fire_conv_gk(const Ctx& c, std::vector<ConvProb>& probs, int mode, int gk, i
         }
         Timer t(plan, 1, c.stream);
         int e = gk == 8   ? launch_conv(L, tiles, plan->dtype, mode, 4, wn, wm, c.stream)
+                : gk == 9 ? launch_sgemm(L, tiles, mode, c.stream)
                 : gk >= 6 ? launch_hgemm(L, tiles, mode, gk == 7 ? 64 : GEMM_BN, c.stream)
                 : gk >= 4 ? launch_gemm(L, tiles, mode, gk == 5 ? 64 : GEMM_BN, c.stream)
                         : launch_conv(L, tiles, plan->dtype, mode, gk, wn, wm, c.stream);
@@ -877,26 +878,36 @@ bool hgemm_ok(const ConvProb& p, int tn) {
          cdiv(p.M, HG_BM) * (p.ncol / tn) >= HG_MIN_TILES;
 }
 
+// A GEMM problem for the short halo GEMM kernel (where 256-pixel tiles are too few, above).  From 32 / 64 / 128 /
+// 192 of its tiles (below, gemm_conv_kernel, its K split): VGG layers of two images at 192 px 494 / 485 / 510 /
+// 512 us, the paper's coarse blocks at 24 px, batch 40 1812 / 1777 / 1830 / 1867 us, VGG layers of nine
+// images at 96 px 493 / 470 / 476 / 516 us
+constexpr long SG_MIN_TILES = 64;
+bool sgemm_ok(const ConvProb& p) {
+  return p.Q <= SG_FLATW && (long)p.M * p.Cg * 2 < (1L << 32) && (long)p.ncol * p.K * 2 < (1L << 31) &&
+         (long)p.M * p.ncol < (1L << 40) && cdiv(p.M, GEMM_BM) * (p.ncol / 64) >= SG_MIN_TILES;
+}
+
 // Gather kind of a convolution problem: 0 pointwise, 1 vector gather, 2 element-wise gather,
 // 3 halo tile, 4 the GEMM kernel with 128-column tiles, 5 with 64-column tiles, 6 and 7 the halo
-// GEMM kernel likewise, 8 flat tiles.
+// GEMM kernel likewise, 8 flat tiles, 9 the short halo GEMM kernel.
 int gather_kind(const ConvProb& p, int es) {
   if (p.Cg % (16 / es) != 0) return 2;
   if (p.k == 1 && p.stride == 1 && p.pad == 0) return 0;
   const int tn = gemm_tn(p, es);
-  if (tn != 0) return (tn == GEMM_BN ? 4 : 5) + (hgemm_ok(p, tn) ? 2 : 0);
+  if (tn != 0) return hgemm_ok(p, tn) ? (tn == GEMM_BN ? 6 : 7) : sgemm_ok(p) ? 9 : tn == GEMM_BN ? 4 : 5;
   if (halo_ok(p, es)) return 3;
   return flat_ok(p, es) ? 8 : 1;
 }
 
 // one grouped launch per (gather kind, column sub-tiles, tall / short tiles)
 int fire_conv(const Ctx& c, std::vector<ConvProb>& probs, int mode) {
-  std::vector<ConvProb> by[9][3][2];
+  std::vector<ConvProb> by[10][3][2];
   for (auto& p : probs) {
     const int w = p.wn == 1 ? 0 : p.wn == 2 ? 1 : 2;
     const int gk = gather_kind(p, c.plan->es);
     ConvProb q = p;
-    if (gk >= 4 && gk < 8) q.tiles_n = q.ncol / (gk % 2 == 0 ? GEMM_BN : 64);
+    if (gk >= 4 && gk != 8) q.tiles_n = q.ncol / (gk % 2 == 0 ? GEMM_BN : 64);
     by[gk][w][p.wm == conv_wm(p.wn, false) ? 0 : 1].push_back(q);
   }
   // GEMM launches: the longest K first, so that the longest tiles start first; the problems with
@@ -944,7 +955,7 @@ int fire_conv(const Ctx& c, std::vector<ConvProb>& probs, int mode) {
         koff += need;
         split.push_back(q);
       }
-  for (int gk = 0; gk < 9; ++gk)
+  for (int gk = 0; gk < 10; ++gk)
     for (int w = 0; w < 3; ++w)
       for (int t = 0; t < 2; ++t) {
         if (by[gk][w][t].empty()) continue;
@@ -1030,7 +1041,8 @@ bool plan_splits_k(const pnn_plan* plan) {
           p.M = plan->B * p.P * p.Q;
           p.K = n.k * n.k * p.Cg;
           set_tiles(p, S.short_tiles);
-          if (gather_kind(p, plan->es) == 4 && cdiv(p.M, GEMM_BM) * (p.ncol / GEMM_BN) < GEMM_SPLIT_BELOW)
+          const int gk = gather_kind(p, plan->es);
+          if ((gk == 4 || (gk == 9 && p.ncol % GEMM_BN == 0)) && cdiv(p.M, GEMM_BM) * (p.ncol / GEMM_BN) < GEMM_SPLIT_BELOW)
             return true;
         }
       }

@@ -330,6 +330,10 @@ constexpr int HG_BM = 256;
 constexpr int HG_AROWS = 376;                   // input pixels staged per workgroup, at most (a multiple of 8)
 constexpr int HG_FLATW = (HG_AROWS - HG_BM - 2) / 2;   // widest map whose flat halo (W + 1 on both sides) fits
 int launch_hgemm(const ConvLaunch& L, int tiles, int mode, int tn, hipStream_t s);   // tn: 128 or 64
+// the same of fewer pixels, with or without a prologue: GEMM_BM pixels x 64 columns per workgroup
+constexpr int SG_AROWS = 200;
+constexpr int SG_FLATW = (SG_AROWS - GEMM_BM - 2) / 2;
+int launch_sgemm(const ConvLaunch& L, int tiles, int mode, hipStream_t s);
 // the split problems' second pass: partial tiles summed in split order, then the epilogue, one
 // workgroup per GEMM_RBN-column slab of a tile
 int launch_gemm_reduce(const ConvLaunch& L, int tiles, int mode, hipStream_t s);
