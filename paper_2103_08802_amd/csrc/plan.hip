@@ -1734,7 +1734,10 @@ int run_bwd(const Ctx& c, const std::vector<const SegP*>& segs, const std::vecto
 // fp32 network (0.4 MB) 177 / 283, ResNet units of 9 MB 408 / 561, of 30 MB 375 / 388, of 150 MB 915 / 865,
 // of 300 MB 1914 / 1651.  Plans with K-split GEMM problems (VGG) keep their chains: how such a problem is split,
 // and with it the order of its sums, depends on the problems it shares a call with.
-constexpr size_t CHAIN_MIN_BYTES = (size_t)40 << 20;
+// The fp32 products take several times as long per byte, so there the chains of a few large sub-networks pay
+// earlier (one / four streams, us: three units of 13 to 17 MB 515 / 393 and 580 / 432, of 7 MB 464 / 385, of 3.3 MB
+// 422 / 395; six of 5.5 MB 569 / 568, of 2 MB 513 / 539; twelve of 1.3 MB 478 / 567).
+constexpr size_t CHAIN_MIN_BYTES = (size_t)40 << 20, CHAIN_MIN_F32 = (size_t)4 << 20;   // (the latter per sub-network)
 struct Chains {
   std::vector<std::vector<const SegP*>> segs;
   std::vector<std::vector<Ptrs>> ptrs;
@@ -1748,7 +1751,7 @@ int chains_group(const Ctx& c, const std::vector<const SegP*>& segs, const std::
   pnn_plan* p = c.plan;
   size_t saved = 0;
   for (auto* sp : segs) saved += sp->saved_bytes;
-  const bool few = saved < CHAIN_MIN_BYTES && p->kpart_stride == 0;
+  const bool few = saved < CHAIN_MIN_BYTES && (p->es == 2 || saved < CHAIN_MIN_F32 * segs.size()) && p->kpart_stride == 0;
   const int maxg = p->timing_family != 0 || few ? 1 : std::min(p->streams, (int)p->side.size() + 1);
   std::vector<long> keys;
   for (size_t i = 0; i < segs.size(); ++i) {
