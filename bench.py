@@ -74,7 +74,8 @@ KERNEL_SOURCES = {
 COPY_BYTES = 256 << 20          # the --copy-calibration copy
 # the kernels of a family: the launches the library's timing family covers (conv: every forward
 # and data-gradient convolution launch, the GEMM kernel's and its split-K reduce's included)
-FAMILY_KERNELS = {"conv_kernel": ("conv_kernel", "gemm_conv_kernel", "hgemm_conv_kernel", "sgemm_conv_kernel", "gemm_reduce_kernel")}
+FAMILY_KERNELS = {"conv_kernel": ("conv_kernel", "gemm_conv_kernel", "hgemm_conv_kernel", "sgemm_conv_kernel",
+                                  "gemm_reduce_kernel")}
 
 
 def _sources_sha(kernel):
@@ -322,8 +323,8 @@ def summarize_trace(stats_csv, trace_csv, out_md, title, cmd):
         t = fam.setdefault(n, [0, 0.0])
         t[0] += 1
         t[1] += d
-    # every step runs the head once: its dispatch count is the number of steps in the run
-    steps = fam.get("head_sample_kernel", [0, 0.0])[0]
+    # every step runs the head once (in one of its two forms): its dispatch count is the number of steps in the run
+    steps = fam.get("head_sample_kernel", [0, 0.0])[0] + fam.get("head_pool_kernel", [0, 0.0])[0]
     with open(out_md, "w") as f:
         f.write(f"# {title}\n\nCommand (from the repository root, on one MI355X):\n\n```\n{cmd}\n```\n\n")
         f.write("Per kernel family, all dispatches of the run (warm-up, timed and instrumented steps):\n\n")

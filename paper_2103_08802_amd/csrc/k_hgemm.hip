@@ -515,7 +515,8 @@ int launch_sgemm(const ConvLaunch& L, int tiles, int mode, hipStream_t s) {
 // Pixels run over rows padded by one column, u = row (W + 1) + x with x = W a pad of zeros, so that the input
 // pixel of tap s is u + s - 1 with no test at the image's sides: the pads multiply to zero, and one pad
 // serves the right side of its row and the left side of the next.  Pads, rows outside the image (r = 0, 2)
-// and pixels past the end are loaded from a line of zeros.
+// and pixels past the end are loaded from a line of zeros.  (A pad's zero gradient meets input pixels of the
+// neighbouring column: an infinity there reaches all taps of its row as NaN, not only those it belongs to.)
 //
 // Stages of 64 pixels, pixel-major; fragments by the transposed LDS read, which takes 32 bytes from each of
 // four consecutive rows per 16 lanes, two such groups eight rows apart at a time: the 32-byte pieces of a
