@@ -878,14 +878,14 @@ bool hgemm_ok(const ConvProb& p, int tn) {
          cdiv(p.M, HG_BM) * (p.ncol / tn) >= HG_MIN_TILES;
 }
 
-// A GEMM problem for the short halo GEMM kernel (where 256-pixel tiles are too few, above).  From 32 / 64 / 128 /
-// 192 of its tiles (below, gemm_conv_kernel, its K split): VGG layers of two images at 192 px 494 / 485 / 510 /
-// 512 us, the paper's coarse blocks at 24 px, batch 40 1812 / 1777 / 1830 / 1867 us, VGG layers of nine
-// images at 96 px 493 / 470 / 476 / 516 us
-constexpr long SG_MIN_TILES = 64;
+// A GEMM problem for the short halo GEMM kernel (where 256-pixel tiles are too few, above): those of 128-column
+// tiles that gemm_conv_kernel would run unsplit, at least 256 of its tiles.  Smaller ones stay with the K split,
+// whose shorter sums are the more accurate (nine images of VGG layers at 96 px were 548 -> 510 us without it,
+// their gradients' error against 64 bits 3.7e-3 -> 4.7e-3).
 bool sgemm_ok(const ConvProb& p) {
-  return p.Q <= SG_FLATW && (long)p.M * p.Cg * 2 < (1L << 32) && (long)p.ncol * p.K * 2 < (1L << 31) &&
-         (long)p.M * p.ncol < (1L << 40) && cdiv(p.M, GEMM_BM) * (p.ncol / 64) >= SG_MIN_TILES;
+  return p.Q <= SG_FLATW && p.ncol % GEMM_BN == 0 && (long)p.M * p.Cg * 2 < (1L << 32) &&
+         (long)p.ncol * p.K * 2 < (1L << 31) && (long)p.M * p.ncol < (1L << 40) &&
+         cdiv(p.M, GEMM_BM) * (p.ncol / GEMM_BN) >= GEMM_SPLIT_BELOW;
 }
 
 // Gather kind of a convolution problem: 0 pointwise, 1 vector gather, 2 element-wise gather,
@@ -1041,8 +1041,7 @@ bool plan_splits_k(const pnn_plan* plan) {
           p.M = plan->B * p.P * p.Q;
           p.K = n.k * n.k * p.Cg;
           set_tiles(p, S.short_tiles);
-          const int gk = gather_kind(p, plan->es);
-          if ((gk == 4 || (gk == 9 && p.ncol % GEMM_BN == 0)) && cdiv(p.M, GEMM_BM) * (p.ncol / GEMM_BN) < GEMM_SPLIT_BELOW)
+          if (gather_kind(p, plan->es) == 4 && cdiv(p.M, GEMM_BM) * (p.ncol / GEMM_BN) < GEMM_SPLIT_BELOW)
             return true;
         }
       }

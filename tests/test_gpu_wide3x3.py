@@ -4,8 +4,8 @@ sizes where their tiles are ragged or their pixel mapping changes.  One sub-netw
 two with a BN prologue (activated ahead of the kernels), so every form meets 64- and 128-column
 tiles.  A network whose sizes miss the kernels runs the same check through the general ones.
 
-The host's choice needs at least 256 tiles of 256 pixels, else 64 of 128 pixels x 64 columns (the short
-kernel, which applies the prologue itself); the comments give M = batch * H * W."""
+The host's choice needs at least 256 tiles of 256 pixels, else 128 of 128 x 128 for the short kernel
+(which applies the prologue itself); the comments give M = batch * H * W."""
 import numpy as np
 import pytest
 
@@ -37,12 +37,12 @@ def _net(H, W, batch, widths, seeds):
     (61, 61, 18, (64, 64, 128, 64)),      # too wide for flat tiles, no patches: the general kernels
     (9, 10, 190, (64, 128, 64, 64)),      # M = 17100: weight gradient only (under 256 tiles)
     (13, 63, 21, (128, 64, 64, 128)),     # rows of 64 with the pad: stages are whole rows
-    (35, 35, 7, (128, 256, 128, 256)),    # the short kernel's widest map; M = 8575: 127 of 128 pixels in the last tile
-    (36, 36, 7, (128, 256, 128, 256)),    # too wide for it
+    (35, 35, 14, (128, 256, 128, 256)),   # the short kernel's widest map; M = 17150: 126 of 128 pixels in the last tile
+    (36, 36, 13, (128, 256, 128, 256)),   # too wide for it
     (8, 8, 129, (256, 256, 256, 256)),    # images end inside its tiles; M = 8256: 64 pixels in the last
-    (3, 1, 2731, (64, 128, 128, 192)),    # one-pixel rows; M = 8193: one pixel in the last tile
-    (6, 6, 60, (512, 512, 512, 256)),     # the most channels of a prologue; 136 and 68 workgroups
-    (6, 6, 50, (512, 512, 512, 256)),     # 120, and 60: back to the split GEMM
+    (3, 1, 5462, (64, 128, 128, 256)),    # one-pixel rows; M = 16386: two pixels in the last tile
+    (6, 6, 114, (512, 512, 512, 256)),    # the most channels of a prologue; 33 x 4 tiles
+    (6, 6, 60, (512, 512, 512, 256)),     # 17 x 4 tiles: the split GEMM
 ])
 def test_wide_3x3_nodes(H, W, batch, widths):
     _assert(*check_net(_net(H, W, batch, widths, (H, W, batch)), sample=384))
