@@ -880,7 +880,7 @@ bool hgemm_ok(const ConvProb& p, int tn) {
 
 // A GEMM problem for the short halo GEMM kernel (where 256-pixel tiles are too few, above): those of 128-column
 // tiles that gemm_conv_kernel would run unsplit, at least 256 of its tiles.  Smaller ones stay with the K split,
-// whose shorter sums are the more accurate (nine images of VGG layers at 96 px were 548 -> 510 us without it,
+// whose shorter sums are the more accurate (nine images of VGG layers at 96 px 533 -> 510 us without it,
 // their gradients' error against 64 bits 3.7e-3 -> 4.7e-3).
 bool sgemm_ok(const ConvProb& p) {
   return p.Q <= SG_FLATW && p.ncol % GEMM_BN == 0 && (long)p.M * p.Cg * 2 < (1L << 32) &&
