@@ -30,6 +30,8 @@
 #include "pnn_internal.h"
 #include "conv_epilogue.h"
 
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 is a reserved register: clobbering it is what is meant
+
 namespace pnn {
 
 namespace {
@@ -40,9 +42,12 @@ constexpr int HM = HG_BM;                         // output pixels per workgroup
 constexpr int HROW = 128;                         // LDS bytes of a row: 64 channels
 constexpr int HA_ROWS = HG_AROWS;                 // input rows staged, at most (a multiple of 8)
 
-// 64 lanes' 16 bytes each (base + voff per lane) into LDS bytes [lds, lds + 1024) in lane order
+// 64 lanes' 16 bytes each (base + voff per lane) into LDS bytes [lds, lds + 1024) in lane order.  A load to LDS
+// needs one wait state after the scalar write of m0 that names its LDS address (the compiler adds it between
+// instructions of its own, not inside an asm block).
 __device__ __forceinline__ void load_lds16(uint32_t lds, const void* base, uint32_t voff) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base)
+               : "memory", "m0");
 }
 // the wave's own global-to-LDS loads have landed; then every wave's have
 __device__ __forceinline__ void lds_ready() {
@@ -532,9 +537,10 @@ __device__ __attribute__((aligned(256))) const uint4 hg_zeros[16] = {};
 typedef short wv4s16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) wv4s16 lds_wv4s16;
 
-// 64 lanes' 16 bytes each (per-lane addresses) into LDS bytes [lds, lds + 1024) in lane order
+// 64 lanes' 16 bytes each (per-lane addresses) into LDS bytes [lds, lds + 1024) in lane order (wait state: above)
 __device__ __forceinline__ void load_lds16(uint32_t lds, const void* addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr)
+               : "memory", "m0");
 }
 
 // XOR of the 16-byte slot of row r (an even number: pairs stay together)
