@@ -94,8 +94,7 @@ struct WgradGeom {
   bool halo3 = false;      // 3x3 / stride 1 / pad 1 through the halo kernel (tiles_k = Cg / 16)
   bool gemm = false;       // wide 3x3 / stride 1 / pad 1 bf16 through the GEMM kernel
   int gtc = 0, gtk = 0;    // its tile: output channels, filter columns (128 or 64)
-  bool row = false;        // without a prologue: the filter-row kernel (launch_wgrad_row), same splits
-  int uchunk = 0;          // its pixels per split, in rows padded by one column
+  bool row = false;        // the filter-row kernel instead (launch_wgrad_row; mchunk in rows padded by one column)
 };
 
 }  // namespace
@@ -193,11 +192,12 @@ WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
       // three taps per workgroup, two workgroups per CU
       const long U = (long)B * n.Ho * (n.Wo + 1);
       splits = std::max(1L, std::min(cdiv(U, 8L * 64), 512 / (base / 3)));
-      g.uchunk = (int)(cdiv(cdiv(U, splits), 64) * 64);
-      splits = cdiv(U, g.uchunk);
+      g.mchunk = (int)(cdiv(cdiv(U, splits), 64) * 64);
+      g.splits = (int)cdiv(U, g.mchunk);
+      return g;
     }
-    g.mchunk = (int)(cdiv(cdiv(M, splits), 64) * 64);   // (a split past the end stores zeros)
-    g.splits = (int)splits;
+    g.mchunk = (int)(cdiv(cdiv(M, splits), 64) * 64);
+    g.splits = (int)cdiv(M, g.mchunk);
     return g;
   }
   const bool whole_rows = kc % n.Wo == 0 && (pq % kc == 0 || kc % pq == 0);
@@ -1064,7 +1064,7 @@ bool act_materialize(const ConvProb& p, int es) {
 }
 
 // Likewise the input of a GEMM weight gradient with a BN prologue (the prologue there activates
-// each input element once per tap and output-channel tile); the filter-row kernel takes no other.
+// each input element once per tap and output-channel tile); the filter-row kernel has no prologue.
 bool wgrad_act(const NodeP& n, int B, int es) {
   if (n.bn < 0) return false;
   const WgradGeom g = wgrad_geom_node(n, B, es);
@@ -1419,9 +1419,44 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
   char* wpart = c.wpart != nullptr ? c.wpart : c.scratch + plan->wpart_off;
   std::vector<WgradProb> wg_vec, wg_gen, wg_h3, wg_pw, wg_gemm, wg_row;
   std::vector<BnActProb> act;          // activated inputs of the GEMM weight gradients (wgrad_act)
-  char* act_region = c.act != nullptr ? c.act : plan->act_stride != 0 ? c.scratch + plan->act_off : nullptr;
+  char* act_region = c.act != nullptr ? c.act : c.scratch + plan->act_off;
   size_t act_used = 0;
   size_t woff = 0;
+  auto fire = [&](std::vector<WgradProb>& list, int v) {
+    return grouped<WgradLaunch>(
+        list, [v](const WgradProb& p) { return p.tiles_co * p.tiles_k / (v >= 8 ? 3 : 1) * p.splits; },
+        [&](const WgradLaunch& Lx, int tiles, size_t) {
+          double fl = 0, by = 0;
+          for (int i = 0; i < Lx.n; ++i) {
+            const WgradProb& p = Lx.p[i];
+            fl += 2.0 * p.M * (double)p.Co * p.K;
+            by += (double)p.M * p.Co * es + (double)p.B * p.H * p.W * p.Cg * es + (double)p.Co * p.K * 4;
+          }
+          Timer t(plan, 2, c.stream);
+          int e2 = v == 2   ? launch_wgrad3(Lx, tiles, plan->dtype, c.stream)
+                   : v >= 8 ? launch_wgrad_row(Lx, tiles, Lx.p[0].gtc, Lx.p[0].gtk, c.stream)
+                   : v >= 4 ? launch_wgrad_gemm(Lx, tiles, Lx.p[0].gtc, Lx.p[0].gtk, c.stream)
+                            : launch_wgrad(Lx, tiles, plan->dtype, v == 0 ? WG_VEC : v == 1 ? WG_GEN : WG_PW,
+                                           c.stream);
+          t.done(c.stream, fl, by);
+          return e2;
+        });
+  };
+  // the GEMM and filter-row problems so far, behind their activated inputs (one launch per tile shape)
+  auto fire_gemm = [&]() -> int {
+    int e = grouped<BnActLaunch>(
+        act, [](const BnActProb& q) { return (int)cdiv(q.n_out, q.pix); },
+        [&](const BnActLaunch& Lx, int tiles, size_t) { return launch_bnact_fwd(Lx, tiles, plan->dtype, c.stream); });
+    std::vector<WgradProb> by[8];   // (4 ..: the filter-row kernel)
+    for (const WgradProb& p : wg_gemm) by[(p.gtc == 128 ? 0 : 2) + (p.gtk == 128 ? 0 : 1)].push_back(p);
+    for (const WgradProb& p : wg_row) by[4 + (p.gtc == 128 ? 0 : 2) + (p.gtk == 128 ? 0 : 1)].push_back(p);
+    for (int v = 0; v < 8 && e == 0; ++v) e = fire(by[v], 4 + v);
+    act.clear();
+    act_used = 0;
+    wg_gemm.clear();
+    wg_row.clear();
+    return e;
+  };
   for (size_t i = 0; i < segs.size(); ++i) {
     const SegP& S = *segs[i];
     const Ptrs& P = ptrs[i];
@@ -1439,8 +1474,14 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
       WgradGeom g = wgrad_geom_node(n, B, es);
       p.wr = g.wr; p.tiles_co = g.tiles_co; p.tiles_k = g.tiles_k; p.splits = g.splits; p.mchunk = g.mchunk;
       p.gtc = g.gtc; p.gtk = g.gtk;
-      const size_t abytes = (size_t)B * n.H * n.W * n.cin * es;
-      if (act_region != nullptr && wgrad_act(n, B, es) && act_used + abytes <= plan->act_stride) {
+      if (wgrad_act(n, B, es)) {
+        // The region holds the inputs of one level (act_level_bytes), so any one of them.  Every level at once
+        // may need more: what has been collected goes first, and the region is reused in stream order.
+        const size_t abytes = (size_t)B * n.H * n.W * n.cin * es;
+        if (act_used + abytes > plan->act_stride) {
+          const int e = fire_gemm();
+          if (e) return e;
+        }
         BnActProb a;
         std::memset(&a, 0, sizeof(a));
         a.z = p.in;
@@ -1467,9 +1508,7 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
       } else {
         const bool vec = n.cin % (16 / es) == 0;
         const bool pw = vec && n.k == 1 && n.stride == 1 && n.pad == 0;
-        const bool row = g.row && p.pro == nullptr;   // (a full activation region leaves the prologue)
-        if (row) p.mchunk = g.uchunk;
-        (row ? wg_row : g.gemm ? wg_gemm : g.halo3 ? wg_h3 : pw ? wg_pw : vec ? wg_vec : wg_gen).push_back(p);
+        (g.row ? wg_row : g.gemm ? wg_gemm : g.halo3 ? wg_h3 : pw ? wg_pw : vec ? wg_vec : wg_gen).push_back(p);
       }
       ColRedProb r;
       std::memset(&r, 0, sizeof(r));
@@ -1482,39 +1521,13 @@ int fire_wgrads(const Ctx& c, const std::vector<const SegP*>& segs, const std::v
       red.push_back(r);
     }
   }
-  {
-    const int e = grouped<BnActLaunch>(
-        act, [](const BnActProb& q) { return (int)cdiv(q.n_out, q.pix); },
-        [&](const BnActLaunch& Lx, int tiles, size_t) { return launch_bnact_fwd(Lx, tiles, plan->dtype, c.stream); });
-    if (e) return e;
+  int e = PNN_OK;
+  int v = 0;
+  for (auto* list : {&wg_vec, &wg_gen, &wg_h3, &wg_pw}) {
+    if (e == 0) e = fire(*list, v);
+    ++v;
   }
-  // the GEMM problems by tile shape (one launch per shape)
-  std::vector<WgradProb> wg_gemm_by[8];   // (4 ..: the filter-row kernel)
-  for (const WgradProb& p : wg_gemm) wg_gemm_by[(p.gtc == 128 ? 0 : 2) + (p.gtk == 128 ? 0 : 1)].push_back(p);
-  for (const WgradProb& p : wg_row) wg_gemm_by[4 + (p.gtc == 128 ? 0 : 2) + (p.gtk == 128 ? 0 : 1)].push_back(p);
-  for (int v = 0; v < 12; ++v) {
-    auto& list = v == 0 ? wg_vec : v == 1 ? wg_gen : v == 2 ? wg_h3 : v == 3 ? wg_pw : wg_gemm_by[v - 4];
-    int e = grouped<WgradLaunch>(
-        list, [v](const WgradProb& p) { return p.tiles_co * p.tiles_k / (v >= 8 ? 3 : 1) * p.splits; },
-        [&](const WgradLaunch& Lx, int tiles, size_t) {
-          double fl = 0, by = 0;
-          for (int i = 0; i < Lx.n; ++i) {
-            const WgradProb& p = Lx.p[i];
-            fl += 2.0 * p.M * (double)p.Co * p.K;
-            by += (double)p.M * p.Co * es + (double)p.B * p.H * p.W * p.Cg * es + (double)p.Co * p.K * 4;
-          }
-          Timer t(plan, 2, c.stream);
-          int e2 = v == 2   ? launch_wgrad3(Lx, tiles, plan->dtype, c.stream)
-                   : v >= 8 ? launch_wgrad_row(Lx, tiles, Lx.p[0].gtc, Lx.p[0].gtk, c.stream)
-                   : v >= 4 ? launch_wgrad_gemm(Lx, tiles, Lx.p[0].gtc, Lx.p[0].gtk, c.stream)
-                            : launch_wgrad(Lx, tiles, plan->dtype, v == 0 ? WG_VEC : v == 1 ? WG_GEN : WG_PW,
-                                           c.stream);
-          t.done(c.stream, fl, by);
-          return e2;
-        });
-    if (e) return e;
-  }
-  return PNN_OK;
+  return e == 0 ? fire_gemm() : e;
 }
 
 // Backward of a set of segments run together, level by level.  wgrad = false leaves the weight

@@ -186,6 +186,37 @@ def test_coarse_bwd_all_equals_per_block_calls():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("form,batch,n_sub,units", [
+    ("paper", 32, 12, 4),       # one two-3x3 unit per block; 32768 pixels of 64 channels, 8192 of 128
+    ("paper", 130, 4, 4),       # three units per block, 64 to 256 channels past 8192 pixels; ragged tiles
+    ("vgg", 128, 4, 0),         # 3x3 blocks of 64 to 512 channels
+])
+def test_coarse_routes_agree(form, batch, n_sub, units):
+    """The coarse gradients of the per-block calls, of coarse_bwd_all and of parareal_bwd are bit-identical where
+    the blocks' 3x3 layers are wide: their weight gradients' kernel and order of sums do not depend on
+    which blocks share a call."""
+    import torch
+    from paper_2103_08802_amd.step import ParaRealGPU
+    if form == "vgg":
+        net = vgg_parareal("vgg-routes", batch, 32, 10, "bf16", (4, 5, 6), coarse="config")
+    else:
+        net = resnet_parareal(f"resnet-routes-{form}", batch, 32, n_sub, 10, "bf16", (4, 5, 6), coarse=form,
+                              units_per_stage=units)
+    x, labels, params = S.make_all(net)
+    out = []
+    for chain_all, overlap in ((False, False), (True, False), (True, True)):
+        g = ParaRealGPU(net, params)
+        g.coarse_chain_all, g.overlap_bwd = chain_all, overlap
+        g.load_input(x, labels)
+        g.forward()
+        g.backward_coarse_fine()
+        torch.cuda.synchronize()
+        out.append([t.clone() for t in g.D + g.deta + g.dphi + g.dx])
+    bad = [(r, i) for r in (1, 2) for i, (a, b) in enumerate(zip(out[0], out[r])) if not torch.equal(a, b)]
+    assert not bad, bad
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("idx,batch", [(1, 2), (2, 2), (3, 4)])
 def test_streams_do_not_change_results(idx, batch):
     """Running the fine sub-network groups on separate streams gives bit-identical loss, logits and
