@@ -33,7 +33,6 @@ struct NodeP {
   size_t w_off = NONE, gw_off = NONE, wt_off = NONE;
   bool dgrad = false;      // data gradient needed in the backward
   bool first_of_two = false;
-  bool alone = false;      // its launches hold one problem (a coarse block's)
   bool resident = false;   // part of the segment's run of resident units (unit_fwd_kernel)
 };
 
@@ -154,16 +153,16 @@ WgradGeom wgrad_geom(const NodeP& n, long M, int es);
 constexpr long WGROW_MIN_M = 8192;
 
 // Stages per split of the halo weight gradient and rows per split of the general one.  A launch with fewer
-// workgroups than CUs runs at one split's latency, so splits are shorter where a launch holds one problem
-// (coarse blocks, `alone`: 2.51 -> 2.31 ms), in fp32 (units 756 -> 720 us) and in problems of under 32
-// workgroups (fp32 network 174 -> 145 us); elsewhere the sub-networks' other problems fill the launch and shorter
-// splits only add partial rows (ResNet-1001 step 13.5 -> 13.7 ms at half, 13.9 to 14.2 at a quarter).
+// workgroups than CUs runs at one split's latency, so splits are shorter in fp32 (units 756 -> 720 us) and in
+// problems of under 32 workgroups (fp32 network 174 -> 145 us); elsewhere other problems fill the launch and shorter
+// splits only add partial rows (ResNet-1001 step 13.5 -> 13.7 ms at half, 13.9 to 14.2 at a quarter; a quarter for
+// its coarse blocks alone, which share one launch in a step: coarse_bwd_all 1179 -> 1272 us).
 struct WgradRows {
-  long usual, alone, f32, few;
+  long usual, f32, few;
 };
-constexpr WgradRows W3_STAGES{4, 2, 2, 1}, WG_ROWS{512, 128, 256, 128};
-long wgrad_rows(const WgradRows& r, const NodeP& n, long wg, int es) {   // wg: workgroups at the usual split
-  return wg < 32 ? r.few : wg < 300 && n.alone ? r.alone : wg < 300 && es == 4 ? r.f32 : r.usual;
+constexpr WgradRows W3_STAGES{4, 2, 1}, WG_ROWS{512, 256, 128};
+long wgrad_rows(const WgradRows& r, long wg, int es) {   // wg: workgroups at the usual split
+  return wg < 32 ? r.few : wg < 300 && es == 4 ? r.f32 : r.usual;
 }
 
 WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
@@ -212,7 +211,7 @@ WgradGeom wgrad_geom_node(const NodeP& n, int B, int es) {
       g.tiles_co = n.cout / 16;
       g.tiles_k = n.cin / 16;
       const long base = (long)g.tiles_co * g.tiles_k;
-      const long stages = wgrad_rows(W3_STAGES, n, base * cdiv(M, W3_STAGES.usual * kc), es);
+      const long stages = wgrad_rows(W3_STAGES, base * cdiv(M, W3_STAGES.usual * kc), es);
       long splits = std::max(1L, std::min(cdiv(M, stages * kc), cdiv(256, base)));
       g.mchunk = (int)(cdiv(cdiv(M, splits), kc) * kc);
       g.splits = (int)cdiv(M, g.mchunk);
@@ -229,7 +228,7 @@ WgradGeom wgrad_geom(const NodeP& n, long M, int es) {
   g.tiles_co = Co / (16 * g.wr);
   g.tiles_k = (int)cdiv(K, 64);
   const long base = (long)g.tiles_co * g.tiles_k;
-  const long rows = wgrad_rows(WG_ROWS, n, base * cdiv(M, WG_ROWS.usual), es);
+  const long rows = wgrad_rows(WG_ROWS, base * cdiv(M, WG_ROWS.usual), es);
   long splits = std::max(1L, std::min(cdiv(M, rows), cdiv(1024, base)));
   long mchunk = cdiv(cdiv(M, splits), 128) * 128;
   g.mchunk = (int)mchunk;
@@ -271,9 +270,10 @@ int pw_wm(long M, int ncol, bool short_ok) {
 // launch (EPI_PW_WGRAD) when every output channel row is a whole 16-row MFMA tile and its split-K
 // partial rows (one per workgroup) fit the region reserved for the weight-gradient kernel's splits.
 // Likewise the BN-sum pass of a deferred-apply BN (bnsum_kernel) for its consumer's weight gradient.
+// Not in the coarse blocks: coarse_bwd_all forms theirs by the weight-gradient kernel, whose order of sums is another.
 // Returns the partial rows (the launch's row tiles), or 0 when the weight gradient is not fused.
 long wgrad_fused_rows(const SegP& S, const NodeP& n, int B, int es) {
-  if (n.op != PNN_OP_CONV || !n.dgrad || n.bn < 0 || n.cout % 16 != 0) return 0;
+  if (n.op != PNN_OP_CONV || !n.dgrad || n.bn < 0 || n.cout % 16 != 0 || S.part == 2) return 0;
   const long M = (long)B * n.Ho * n.Wo;
   long tiles_m = 0;
   if (pw_bwd_node(S, n, es))
@@ -317,7 +317,6 @@ pnn_status build_segment(const pnn_segment_desc& d, int part, int index, int B, 
     NodeP n;
     n.op = x.op; n.src = x.src; n.dst = x.dst; n.bn = x.bn; n.pool = x.pool; n.k = x.k;
     n.stride = x.stride; n.pad = x.pad; n.cout = x.cout; n.res = x.res;
-    n.alone = S.short_tiles;
     if (n.src < 0 || n.src >= n_slots || !made[n.src]) return PNN_ERR_SHAPE;
     if (n.dst <= 0 || n.dst >= n_slots || made[n.dst]) return PNN_ERR_SHAPE;
     if (n.res >= n_slots || (n.res >= 0 && !made[n.res])) return PNN_ERR_SHAPE;

@@ -186,21 +186,24 @@ def test_coarse_bwd_all_equals_per_block_calls():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("form,batch,n_sub,units", [
-    ("paper", 32, 12, 4),       # one two-3x3 unit per block; 32768 pixels of 64 channels, 8192 of 128
-    ("paper", 130, 4, 4),       # three units per block, 64 to 256 channels past 8192 pixels; ragged tiles
-    ("vgg", 128, 4, 0),         # 3x3 blocks of 64 to 512 channels
+@pytest.mark.parametrize("form,batch,n_sub,units,dtype", [
+    ("paper", 32, 12, 4, "bf16"),       # one two-3x3 unit per block; 32768 pixels of 64 channels, 8192 of 128
+    ("paper", 130, 4, 4, "bf16"),       # three units per block, 64 to 256 channels past 8192 pixels; ragged tiles
+    ("config", 128, 8, 8, "bf16"),      # bottleneck blocks
+    ("config", 512, 3, 2, "bf16"),
+    ("config", 3, 4, 4, "bf16"),
+    ("config", 128, 8, 8, "f32"),
+    ("vgg", 128, 4, 0, "bf16"),         # 3x3 blocks of 64 to 512 channels
 ])
-def test_coarse_routes_agree(form, batch, n_sub, units):
-    """The coarse gradients of the per-block calls, of coarse_bwd_all and of parareal_bwd are bit-identical where
-    the blocks' 3x3 layers are wide: their weight gradients' kernel and order of sums do not depend on
-    which blocks share a call."""
+def test_coarse_routes_agree(form, batch, n_sub, units, dtype):
+    """The coarse gradients of the per-block calls, of coarse_bwd_all and of parareal_bwd are bit-identical: the
+    weight gradients' order of sums does not depend on which blocks share a call."""
     import torch
     from paper_2103_08802_amd.step import ParaRealGPU
     if form == "vgg":
-        net = vgg_parareal("vgg-routes", batch, 32, 10, "bf16", (4, 5, 6), coarse="config")
+        net = vgg_parareal("vgg-routes", batch, 32, 10, dtype, (4, 5, 6), coarse="config")
     else:
-        net = resnet_parareal(f"resnet-routes-{form}", batch, 32, n_sub, 10, "bf16", (4, 5, 6), coarse=form,
+        net = resnet_parareal(f"resnet-routes-{form}", batch, 32, n_sub, 10, dtype, (4, 5, 6), coarse=form,
                               units_per_stage=units)
     x, labels, params = S.make_all(net)
     out = []
