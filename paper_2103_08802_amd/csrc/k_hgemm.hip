@@ -30,6 +30,8 @@
 #include "pnn_internal.h"
 #include "conv_epilogue.h"
 
+#include <type_traits>
+
 #pragma clang diagnostic ignored "-Winline-asm"   // m0 is a reserved register: clobbering it is what is meant
 
 namespace pnn {
@@ -520,8 +522,10 @@ int launch_sgemm(const ConvLaunch& L, int tiles, int mode, hipStream_t s) {
 // Pixels run over rows padded by one column, u = row (W + 1) + x with x = W a pad of zeros, so that the input
 // pixel of tap s is u + s - 1 with no test at the image's sides: the pads multiply to zero, and one pad
 // serves the right side of its row and the left side of the next.  Pads, rows outside the image (r = 0, 2)
-// and pixels past the end are loaded from a line of zeros.  (A pad's zero gradient meets input pixels of the
-// neighbouring column: an infinity there reaches all taps of its row as NaN, not only those it belongs to.)
+// and pixels past the end are loaded from a line of zeros.  A pad's zero gradient meets the input pixels on both
+// sides of it, and an infinity there would make a tap NaN that it does not belong to: a workgroup whose sums
+// hold a NaN forms them again with those input pixels cleared too (clearing them in every pass would put vector
+// instructions between the LDS reads and the MFMAs).
 //
 // Stages of 64 pixels, pixel-major; fragments by the transposed LDS read, which takes 32 bytes from each of
 // four consecutive rows per 16 lanes, two such groups eight rows apart at a time: the 32-byte pieces of a
@@ -627,18 +631,20 @@ __global__ __launch_bounds__(256, 2) void wgrad_row_kernel(const WgradLaunch L) 
   };
   Row rg[OG::NW], ra[OA::NW];
   uint32_t cg_[OG::NW], ca_[OA::NW];              // byte offset of the lane's chunk within the tile's channels
+  auto first_rows = [&]() {
 #pragma unroll
-  for (int j = 0; j < OG::NW; ++j) {
-    const int r = OG::RPL * (wave + 4 * j) + lane / (64 / OG::RPL);
-    rg[j] = make_row(u0 + r);
-    cg_[j] = 16 * ((lane % (64 / OG::RPL)) ^ wg2_swz<TC>(r)) + 2 * co0;
-  }
+    for (int j = 0; j < OG::NW; ++j) {
+      const int r = OG::RPL * (wave + 4 * j) + lane / (64 / OG::RPL);
+      rg[j] = make_row(u0 + r);
+      cg_[j] = 16 * ((lane % (64 / OG::RPL)) ^ wg2_swz<TC>(r)) + 2 * co0;
+    }
 #pragma unroll
-  for (int j = 0; j < OA::NW; ++j) {
-    const int r = OA::RPL * (wave + 4 * j) + lane / (64 / OA::RPL);
-    ra[j] = make_row(u0 - 1 + r);
-    ca_[j] = 16 * ((lane % (64 / OA::RPL)) ^ wg2_swz<TK>(r)) + 2 * c0;
-  }
+    for (int j = 0; j < OA::NW; ++j) {
+      const int r = OA::RPL * (wave + 4 * j) + lane / (64 / OA::RPL);
+      ra[j] = make_row(u0 - 1 + r);
+      ca_[j] = 16 * ((lane % (64 / OA::RPL)) ^ wg2_swz<TK>(r)) + 2 * c0;
+    }
+  };
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const char* const gbase = (const char*)P.g;
   const char* const abase = (const char*)P.in;
@@ -680,57 +686,91 @@ __global__ __launch_bounds__(256, 2) void wgrad_row_kernel(const WgradLaunch L) 
       const int r = row_g + s + 4 * h;
       off_a[s][h] = OG::BYTES + r * OA::RB + 16 * (((wc * (TK / 2)) / 8 + bch) ^ wg2_swz<TK>(r)) + bby;
     }
-  auto frag = [&](uint32_t lo, uint32_t hi, Frag<uint16_t>& f) {
+  auto frag = [&](uint32_t lo, uint32_t hi) {
     const wv4s16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_wv4s16*)(uintptr_t)lo);
     const wv4s16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_wv4s16*)(uintptr_t)hi);
     const uint2 l2 = __builtin_bit_cast(uint2, a), h2 = __builtin_bit_cast(uint2, b);
-    f.from_raw(make_uint4(l2.x, l2.y, h2.x, h2.y));
+    return make_uint4(l2.x, l2.y, h2.x, h2.y);
   };
 
   f32x4 acc[3][NI][NJ];
+  // the workgroup's sums (CLEAR: the side taps' input pixels that a pad meets are cleared)
+  auto sums = [&](auto clear) {
+    constexpr bool CLEAR = decltype(clear)::value;
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[s][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    first_rows();
+    issue(0);
+    issue(1);
+    int st = 0;
+#pragma unroll 1
+    for (int n = 0; n < nst; ++n) {
+      // this stage has landed (the next one's loads may be in flight) and every wave is past the stage before
+      // it, whose buffer the stage after the next takes
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(AHEAD) : "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      issue(st == 0 ? 2 : st - 1);                // (past the end: zeros, or input rows that no gradient row meets)
+      const uint32_t b = lds0 + st * STG;
+#pragma unroll
+      for (int sub = 0; sub < WG2_PX / 32; ++sub) {
+        Frag<uint16_t> a[NI], f[3][NJ];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const uint32_t o = b + (off_g ^ (32 * i)) + sub * 32 * OG::RB;
+          a[i].from_raw(frag(o, o + 4 * OG::RB));
+        }
+        uint32_t keep[4] = {~0u, ~0u, ~0u, ~0u};  // the lane's eight pixels, two to a word
+        if constexpr (CLEAR) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if ((u0 + n * WG2_PX + sub * 32 + 8 * grp + e) % W1 == Wd) keep[e / 2] &= e % 2 ? 0xffffu : 0xffff0000u;
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            uint4 v = frag(b + (off_a[s][0] ^ (32 * j)) + sub * 32 * OA::RB,
+                           b + (off_a[s][1] ^ (32 * j)) + sub * 32 * OA::RB);
+            if (CLEAR && s != 1) v = make_uint4(v.x & keep[0], v.y & keep[1], v.z & keep[2], v.w & keep[3]);
+            f[s][j].from_raw(v);
+          }
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+          for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) mma(a[i], f[s][j], acc[s][i][j]);
+      }
+      st = st == NST - 1 ? 0 : st + 1;
+    }
+    // loads past the end are still in flight: they must land before the workgroup's LDS is used again or given back
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  sums(std::false_type{});
+  bool nan = false;
 #pragma unroll
   for (int s = 0; s < 3; ++s)
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[s][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  issue(0);
-  issue(1);
-  int st = 0;
-#pragma unroll 1
-  for (int n = 0; n < nst; ++n) {
-    // this stage has landed (the next one's loads may be in flight) and every wave is past the stage before
-    // it, whose buffer the stage after the next takes
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(AHEAD) : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    issue(st == 0 ? 2 : st - 1);                  // (past the end: zeros, or input rows that no gradient row meets)
-    const uint32_t b = lds0 + st * STG;
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
-    for (int sub = 0; sub < WG2_PX / 32; ++sub) {
-      Frag<uint16_t> a[NI], f[3][NJ];
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const uint32_t o = b + (off_g ^ (32 * i)) + sub * 32 * OG::RB;
-        frag(o, o + 4 * OG::RB, a[i]);
-      }
-#pragma unroll
-      for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-          frag(b + (off_a[s][0] ^ (32 * j)) + sub * 32 * OA::RB, b + (off_a[s][1] ^ (32 * j)) + sub * 32 * OA::RB, f[s][j]);
-#pragma unroll
-      for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) mma(a[i], f[s][j], acc[s][i][j]);
-    }
-    st = st == NST - 1 ? 0 : st + 1;
+        for (int e = 0; e < 4; ++e) nan = nan || acc[s][i][j][e] != acc[s][i][j][e];
+  int* flags = (int*)smem;
+  const int any = __any(nan);
+  __syncthreads();                                // every wave is past its last fragments, and its loads have landed
+  if (lane == 0) flags[wave] = any;
+  __syncthreads();
+  const bool again = (flags[0] | flags[1] | flags[2] | flags[3]) != 0;
+  if (again) {
+    __syncthreads();                              // (the flags have been read)
+    sums(std::true_type{});
   }
-  // loads past the end are still in flight: they must land before the workgroup's LDS is given back
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
   // the partial tile: lane (r16, grp) holds rows 4 grp + e of each 16 x 16 block
 #pragma unroll

@@ -1,0 +1,92 @@
+"""An infinity in one input element reaches exactly the outputs it belongs to: a 3x3 convolution without BN, forward,
+data gradient and weight gradient, against the definition in 64 bits.  Zero operands that only fill a tile (row
+pads, K positions past the end) must not meet it: their product would be NaN."""
+import numpy as np
+import pytest
+
+from pnn_synth import nets
+import pnn_synth as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _taps(x):
+    """The nine input views of a 3x3 / stride 1 / pad 1 convolution and the outputs they belong to."""
+    H, W = x.shape[1:3]
+    for r in range(3):
+        for s in range(3):
+            o = (slice(None), slice(max(0, 1 - r), H - max(0, r - 1)), slice(max(0, 1 - s), W - max(0, s - 1)))
+            i = (slice(None), slice(max(0, r - 1), H - max(0, 1 - r)), slice(max(0, s - 1), W - max(0, 1 - s)))
+            yield r, s, i, o
+
+
+def _conv(x, w):
+    y = np.zeros(x.shape[:3] + (w.shape[0],))
+    for r, s, i, o in _taps(x):
+        y[o] += x[i] @ w[:, r, s].T
+    return y
+
+
+def _conv_t(g, w):
+    d = np.zeros(g.shape[:3] + (w.shape[3],))
+    for r, s, i, o in _taps(g):
+        d[i] += g[o] @ w[:, r, s]
+    return d
+
+
+def _wgrad(x, g, w):
+    dw = np.zeros(w.shape)
+    for r, s, i, o in _taps(x):
+        dw[:, r, s] = g[o].reshape(-1, g.shape[3]).T @ x[i].reshape(-1, x.shape[3])
+    return dw
+
+
+def _same(got, ref, rel):
+    """NaN and infinities where (and of the sign) the reference has them, the rest to rel of its largest value."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref)), (np.isnan(got).sum(), np.isnan(ref).sum())
+    inf = np.isinf(ref)
+    assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], ref[inf])
+    f = np.isfinite(ref)
+    assert np.abs(got[f] - ref[f]).max() <= rel * np.abs(ref[f]).max()
+
+
+@pytest.mark.parametrize("H,W,batch,cin,cout,dtype", [
+    (16, 16, 40, 64, 128, "bf16"),      # filter-row weight gradient, 128 x 64 tiles
+    (7, 45, 33, 128, 64, "bf16"),       # 64 x 128, rows ragged to its stages
+    (24, 40, 40, 64, 64, "bf16"),       # 64 x 64
+    (16, 16, 3, 128, 128, "bf16"),      # too few pixels for it
+    (9, 13, 5, 16, 16, "f32"),
+])
+@pytest.mark.parametrize("where", ["x", "dy"])
+def test_infinity_stays_with_its_taps(H, W, batch, cin, cout, dtype, where):
+    import torch
+    from paper_2103_08802_amd import binding as B
+    from paper_2103_08802_amd.step import ParaRealGPU
+    b = nets._SegBuilder((H, W, cin))
+    fine = b.done(b.conv(0, cout, 3))
+    p = nets._SegBuilder((H, W, 3))
+    net = nets.Net("nonfinite", dtype, batch, (H, W, 3), 10, [p.done(p.conv(0, cin, 1))], [fine], [], cout, (1, 2, 3))
+    _, _, params = S.make_all(net)
+    g = ParaRealGPU(net, params)
+    rng = np.random.default_rng(H * W + cin)
+    x = torch.from_numpy(rng.standard_normal((batch, H, W, cin)).astype(np.float32)).to(g.sdt)
+    dy = torch.from_numpy(rng.standard_normal((batch, H, W, cout)).astype(np.float32)).to(g.sdt)
+    # every corner, side and the middle, each in an image and channel of its own
+    at = [(i, j) for i in (0, H // 2, H - 1) for j in (0, W // 2, W - 1)]
+    t = x if where == "x" else dy
+    for k, (i, j) in enumerate(at):
+        t[k * (batch - 1) // len(at), i, j, k] = float("inf") if k % 2 == 0 else -float("inf")
+    g.x[0].copy_(x)
+    g.D[0].copy_(dy)
+    B.parareal_fine_fwd(g.plan, g.x, g.phi, g.y, g.saved, g.scratch, g.stream())
+    B.parareal_fine_bwd(g.plan, g.D, g.x, g.phi, g.saved, g.dx, g.dphi, g.scratch, g.stream())
+    torch.cuda.synchronize()
+    w = params["fine"][0]["conv"][0]
+    x, dy, w = x.double().numpy(), dy.double().numpy(), np.asarray(w, dtype=np.float64)
+    # stored values: half an ulp of bf16 (2^-8) or fp32 sums of 9 C products; weight gradients: fp32 sums
+    rel = 2.0 ** -8 if dtype == "bf16" else 1e-6
+    with np.errstate(invalid="ignore"):
+        _same(g.to_np(g.y[0]), _conv(x, w), rel)
+        _same(g.to_np(g.dx[0]), _conv_t(dy, w), rel)
+        if where == "x":
+            _same(g.unpack_grads(1, 0)["conv"][0], _wgrad(x, dy, w), 1e-5)
