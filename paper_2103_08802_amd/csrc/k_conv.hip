@@ -346,10 +346,10 @@ __device__ __forceinline__ void conv_flat(const ConvProb& P, const float2* pro, 
 #pragma unroll
   for (int s = 0; s < NKB; ++s) {
     if (s < nsteps) {
-      int k0 = s * KS + VE * grp;
-      if (k0 >= P.K) k0 = 0;                  // (the filter fragment there is zero)
-      const int tap = div_l2(k0, P.Cg, P.cg_log2);
-      const int c0 = k0 - tap * P.Cg;
+      const int k0 = s * KS + VE * grp;
+      const bool in = k0 < P.K;               // past K: the row of zeros, whatever the pixels hold
+      const int tap = in ? div_l2(k0, P.Cg, P.cg_log2) : 9;
+      const int c0 = in ? k0 - tap * P.Cg : 0;
       int r, q;
       tap_rs(tap, 3, r, q);
       const int toff = ((MODE == MODE_FWD) ? ((r - 1) * W + q - 1) : ((1 - r) * W + 1 - q)) * PS + c0;

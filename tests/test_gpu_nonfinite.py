@@ -55,6 +55,7 @@ def _same(got, ref, rel):
     (7, 45, 33, 128, 64, "bf16"),       # 64 x 128, rows ragged to its stages
     (24, 40, 40, 64, 64, "bf16"),       # 64 x 64
     (16, 16, 3, 128, 128, "bf16"),      # too few pixels for it
+    (10, 10, 11, 16, 16, "bf16"),       # flat tiles: K = 144 is no whole number of steps
     (9, 13, 5, 16, 16, "f32"),
 ])
 @pytest.mark.parametrize("where", ["x", "dy"])
