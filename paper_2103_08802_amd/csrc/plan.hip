@@ -1746,9 +1746,13 @@ int run_bwd(const Ctx& c, const std::vector<const SegP*>& segs, const std::vecto
 // of 300 MB 1914 / 1651.  Plans with K-split GEMM problems (VGG) keep their chains: how such a problem is split,
 // and with it the order of its sums, depends on the problems it shares a call with.
 // The fp32 products take several times as long per byte, so there the chains of a few large sub-networks pay
-// earlier (one / four streams, us: three units of 13 to 17 MB 515 / 393 and 580 / 432, of 7 MB 464 / 385, of 3.3 MB
-// 422 / 395; six of 5.5 MB 569 / 568, of 2 MB 513 / 539; twelve of 1.3 MB 478 / 567).
-constexpr size_t CHAIN_MIN_BYTES = (size_t)40 << 20, CHAIN_MIN_F32 = (size_t)4 << 20;   // (the latter per sub-network)
+// earlier, by the bytes that each keeps.  One / four streams, us, on hosts of two speeds: three units of two stages (a
+// chain each) of 1.1 MB 396 / 393 and 395 / 337, of 2.1 MB 422 / 395 and 422 / 343, of 4.2 MB 461 / 389 and
+// 458 / 362, of 8.5 MB 514 / 398; six of 1.4 MB 513 / 539 and 508 / 505, of 2.7 MB 550 / 536, of 5.4 MB 612 / 617;
+// twelve of 0.5 MB 464 / 621, of 1.9 MB 591 / 626.  Sub-networks of one stage share their launches on one stream: two
+// of the fp32 network, 2 MB each, a step 227 / 282, of 3.4 MB 340 / 348, three of 3.4 MB 437 / 427.
+constexpr size_t CHAIN_MIN_BYTES = (size_t)40 << 20, CHAIN_MIN_F32 = (size_t)4 << 20,
+                 CHAIN_MIN_F32_STAGES = (size_t)2 << 20;   // (the latter two per sub-network)
 struct Chains {
   std::vector<std::vector<const SegP*>> segs;
   std::vector<std::vector<Ptrs>> ptrs;
@@ -1761,8 +1765,13 @@ int chains_group(const Ctx& c, const std::vector<const SegP*>& segs, const std::
                  Chains& ch) {
   pnn_plan* p = c.plan;
   size_t saved = 0;
-  for (auto* sp : segs) saved += sp->saved_bytes;
-  const bool few = saved < CHAIN_MIN_BYTES && (p->es == 2 || saved < CHAIN_MIN_F32 * segs.size()) && p->kpart_stride == 0;
+  bool stages = false;
+  for (auto* sp : segs) {
+    saved += sp->saved_bytes;
+    stages = stages || sp->slots[0].H != segs[0]->slots[0].H || sp->slots[0].W != segs[0]->slots[0].W;
+  }
+  const size_t min32 = (stages && segs.size() < 4 ? CHAIN_MIN_F32_STAGES : CHAIN_MIN_F32) * segs.size();
+  const bool few = saved < CHAIN_MIN_BYTES && (p->es == 2 || saved < min32) && p->kpart_stride == 0;
   const int maxg = p->timing_family != 0 || few ? 1 : std::min(p->streams, (int)p->side.size() + 1);
   std::vector<long> keys;
   for (size_t i = 0; i < segs.size(); ++i) {
