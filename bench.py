@@ -65,11 +65,11 @@ def cpu_baseline(idx, batch=24, coarse="config"):
 
 
 # sources a kernel family's code and launch shapes come from; a stored traffic figure is void
-# once any of them changes
+# once the code of any of them changes
 KERNEL_SOURCES = {
     "conv_kernel": ["k_conv.hip", "k_gemm.hip", "k_hgemm.hip", "conv_epilogue.h", "bn_fuse.h", "device_common.h", "pnn_internal.h",
                     "plan.hip"],
-    "wgrad_kernel": ["k_conv.hip", "device_common.h", "pnn_internal.h", "plan.hip"],
+    "wgrad_kernel": ["k_conv.hip", "k_gemm.hip", "k_hgemm.hip", "device_common.h", "pnn_internal.h", "plan.hip"],
 }
 COPY_BYTES = 256 << 20          # the --copy-calibration copy
 # the kernels of a family: the launches the library's timing family covers (conv: every forward
@@ -79,11 +79,13 @@ FAMILY_KERNELS = {"conv_kernel": ("conv_kernel", "gemm_conv_kernel", "hgemm_conv
 
 
 def _sources_sha(kernel):
+    """Hash of the family's sources without their comments and spacing."""
     import hashlib
+    import re
     h = hashlib.sha256()
     for name in KERNEL_SOURCES[kernel]:
-        with open(os.path.join(ROOT, "paper_2103_08802_amd", "csrc", name), "rb") as f:
-            h.update(f.read())
+        with open(os.path.join(ROOT, "paper_2103_08802_amd", "csrc", name)) as f:
+            h.update(" ".join(re.sub(r"//[^\n]*|/\*.*?\*/", " ", f.read(), flags=re.S).split()).encode())
     return h.hexdigest()
 
 
@@ -210,8 +212,8 @@ def summarize_families(fetch_csv, write_csv, trace_csv, out_md, cmd):
         for n, c, fm, wm, us, gbs in rows:
             f.write(f"| `{n}` | {c} | {fm:.1f} | {wm:.1f} | {us:.2f} | {gbs:.0f} |\n")
         f.write("\nPer `conv_kernel` instantiation (template arguments: storage type, mode 0 forward / 1 "
-                "data gradient, gather kind 0 pointwise / 1 vector / 2 element-wise / 3 3x3 halo tile, "
-                "row and column sub-tiles per wave):\n\n")
+                "data gradient, gather kind 0 pointwise / 1 vector / 2 element-wise / 3 3x3 halo tile / 4 3x3 "
+                "flat tile, row and column sub-tiles per wave):\n\n")
         f.write("| instantiation | launches (trace) | fetched MB | written MB | avg us | HBM GB/s |\n"
                 "|---|---:|---:|---:|---:|---:|\n")
         for n, c, fm, wm, us, gbs in irows:

@@ -1,5 +1,5 @@
-// Epilogue of the grouped convolution kernels (forward and data gradient), shared by the
-// implicit-GEMM kernels of k_conv.hip and k_gemm.hip.
+// Epilogue of the grouped convolution kernels (forward and data gradient), shared by the implicit-GEMM
+// kernels of k_conv.hip, k_gemm.hip (and its split-K reduce) and k_hgemm.hip (halo and short halo GEMM).
 #pragma once
 #include "bn_fuse.h"
 #include "device_common.h"

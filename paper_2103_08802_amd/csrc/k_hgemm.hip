@@ -25,7 +25,7 @@
 //
 // K runs channel chunk outer, tap inner, 16 channels per MFMA: the order of gemm_conv_kernel, so the
 // two kernels' results are bit-identical; the fp32 tile goes through the same epilogue in two 128-pixel
-// halves (its BN partial rows).
+// halves (its BN partial rows, of the same pixels in flat tiles and of a patch's half in others).
 #include "device_common.h"
 #include "pnn_internal.h"
 #include "conv_epilogue.h"
@@ -310,7 +310,9 @@ int launch_hgemm(const ConvLaunch& L, int tiles, int mode, int tn, hipStream_t s
 // 16-byte load per lane and step, so no step waits for a load issued in the one before.  A BN prologue is
 // applied in place, once per chunk: a wave activates the rows that it loaded itself two steps earlier.
 //
-// K runs as in gemm_conv_kernel (chunk outer, tap inner): results are bit-identical to its unsplit ones.
+// K runs as in gemm_conv_kernel (chunk outer, tap inner): the convolution's results are bit-identical to its
+// unsplit ones.  The BN partial rows formed with them are not: a thread of a 64-column tile adds every 32nd row of it,
+// of a 128-column tile every 16th.
 // Measured (the paper's coarse blocks, batch 128, 9.7 GFLOP a launch; gemm_conv_kernel before): 256 channels at
 // 8 x 8 pixels, 256 workgroups, forward 50.0 -> 28.2 us, data gradient 39.8 -> 23.5; 128 channels at 16 x 16, 512
 // workgroups, 32.9 -> 22.2 and 26.4 -> 18.1 us (343 to 534 TFLOP/s).

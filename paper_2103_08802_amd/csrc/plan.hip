@@ -878,7 +878,7 @@ bool hgemm_ok(const ConvProb& p, int tn) {
 }
 
 // A GEMM problem for the short halo GEMM kernel (where 256-pixel tiles are too few, above): those of 128-column
-// tiles that gemm_conv_kernel would run unsplit, at least 256 of its tiles.  Smaller ones stay with the K split,
+// tiles that gemm_conv_kernel would run unsplit, at least 128 of its tiles (256 of 64 columns here).  Smaller ones stay with the K split,
 // whose shorter sums are the more accurate (nine images of VGG layers at 96 px 533 -> 510 us without it,
 // their gradients' error against 64 bits 3.7e-3 -> 4.7e-3).
 bool sgemm_ok(const ConvProb& p) {
@@ -1048,8 +1048,8 @@ bool plan_splits_k(const pnn_plan* plan) {
 }
 
 // A forward GEMM problem with a BN prologue that the halo GEMM kernel takes without one, or whose input
-// holds at least ACT_MIN_BYTES: its input is activated once, ReLU(BN(z)) by the BN-ReLU pass into a per-chain region, and the GEMM reads that
-// without a prologue.  The prologue would activate every input element once per tap and column
+// holds at least ACT_MIN_BYTES: its input is activated once, ReLU(BN(z)) by the BN-ReLU pass into a
+// per-chain region, and the GEMM reads that without a prologue.  The prologue would activate every input element once per tap and column
 // tile (9 x ncol / 128 times), which costs the forward GEMM a quarter of its MFMA rate on such
 // layers; the pass costs two tensor passes at the HBM rate.  Results are bit-identical (the same
 // fused multiply-add, ReLU and rounding).

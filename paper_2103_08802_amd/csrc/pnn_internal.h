@@ -325,7 +325,8 @@ constexpr int GEMM_BM = 128, GEMM_BN = 128, GEMM_BK = 64;
 constexpr int CONV_PRO_MAXC = 512;     // largest Cg of a forward BN prologue held in LDS
 int launch_gemm(const ConvLaunch& L, int tiles, int mode, int tn, hipStream_t s);   // tn: 128 or 64
 // large wide 3x3 problems without a prologue (k_hgemm.hip): HG_BM output pixels x tn columns per
-// workgroup, the input pixels of a 64-channel chunk staged once for all taps; bit-identical to launch_gemm
+// workgroup, the input pixels of a 64-channel chunk staged once for all taps; convolution results
+// bit-identical to launch_gemm's (unsplit)
 constexpr int HG_BM = 256;
 constexpr int HG_AROWS = 376;                   // input pixels staged per workgroup, at most (a multiple of 8)
 constexpr int HG_FLATW = (HG_AROWS - HG_BM - 2) / 2;   // widest map whose flat halo (W + 1 on both sides) fits
@@ -349,8 +350,8 @@ constexpr size_t GEMM_KPART_BYTES = (size_t)GEMM_SPLIT_WG * GEMM_BM * GEMM_BN * 
 // filter taps (Cg a multiple of the chunk), or pointwise (1x1 / stride 1 / pad 0: input row m)
 enum { WG_GEN = 0, WG_VEC = 1, WG_PW = 2 };
 int launch_wgrad(const WgradLaunch& L, int tiles, int dtype, int gather, hipStream_t s);
-// wide 3x3 / stride 1 / pad 1 bf16 weight gradients (C_in, C_out multiples of 128) as 128 x 128 GEMM
-// tiles over the pixels (k_gemm.hip); tiles_co = C_out / 128, tiles_k = 9 C_in / 128
+// wide 3x3 / stride 1 / pad 1 bf16 weight gradients as tc x tk GEMM tiles over the pixels (k_gemm.hip);
+// tiles_co = C_out / tc, tiles_k = 9 C_in / tk
 int launch_wgrad_gemm(const WgradLaunch& L, int tiles, int tc, int tk, hipStream_t s);   // tc, tk: 128 or 64
 // large ones without a prologue, one filter row (three taps) per workgroup (k_hgemm.hip): tiles_co x tiles_k / 3
 // workgroups per split; mchunk in pixels of rows padded by one column, a multiple of 64

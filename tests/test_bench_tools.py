@@ -111,3 +111,20 @@ def test_pmc_record_and_source_hash(tmp_path, monkeypatch):
     assert rec["fetch_bytes_per_launch"] == 2 * 1000 * 1024
     assert rec["write_bytes_per_launch"] == 250 * 1024
     assert rec["sources_sha256"] == b._sources_sha("conv_kernel")
+
+
+def test_source_hash_ignores_comments_and_spacing(tmp_path, monkeypatch):
+    """A stored figure stands while a family's code does, whatever is written beside it; the weight-gradient family's
+    code lies in the GEMM sources too."""
+    b = _bench()
+    monkeypatch.setattr(b, "ROOT", str(tmp_path))
+    src = tmp_path / "paper_2103_08802_amd" / "csrc"
+    os.makedirs(src)
+    for names in b.KERNEL_SOURCES.values():
+        for n in names:
+            (src / n).write_text("int f(int a) { return a / 2; }\n")
+    before = {k: b._sources_sha(k) for k in b.KERNEL_SOURCES}
+    (src / "k_hgemm.hip").write_text("// a note\nint f(int a) {  /* another\n   // one */ return a / 2;  // why\n}\n")
+    assert {k: b._sources_sha(k) for k in b.KERNEL_SOURCES} == before
+    (src / "k_hgemm.hip").write_text("int f(int a) { return a / 4; }\n")
+    assert all(b._sources_sha(k) != v for k, v in before.items())
