@@ -104,7 +104,7 @@ struct pnn_plan {
   int img_h = 0, img_w = 0, img_c = 0;
   std::vector<SegP> pre, fine, coarse;
   size_t saved_bytes = 0, scratch_bytes = 0;
-  size_t wpart_off = 0, wpart_bytes = 0;
+  size_t wpart_off = 0;
   size_t head_off = 0, head_bytes = 0;
   size_t sq_off = 0, sq_bytes = 0;
   // resident units: on / off (pnn_set_resident), workgroups that fit the device at once (queried
@@ -120,7 +120,7 @@ struct pnn_plan {
   std::vector<hipStream_t> side;
   std::vector<hipEvent_t> fj;          // fork / join events (no timing), used round robin
   size_t fj_next = 0;
-  size_t wpart_stride = 0;             // one split-K partial region per chain
+  size_t wpart_chains = 0, wpart_stride = 0;   // one split-K partial region per chain, of a level of its sub-networks
   // GEMM-kernel K-split partial tiles: one region per chain like the weight-gradient partials
   // (stride 0: no problem of the plan is split)
   size_t kpart_off = 0, kpart_stride = 0;
@@ -1760,7 +1760,7 @@ struct Chains {
 };
 
 // Groups and their contexts: group g runs on the call's stream (g = 0) or side stream g - 1 and
-// uses split-K partial region g + 1 (region 0 stays with the calls that do not chain).
+// uses split-K partial, K-split and activation regions of its own (the first ones stay with the calls that do not chain).
 int chains_group(const Ctx& c, const std::vector<const SegP*>& segs, const std::vector<Ptrs>& ptrs,
                  Chains& ch) {
   pnn_plan* p = c.plan;
@@ -1809,7 +1809,7 @@ int chains_group(const Ctx& c, const std::vector<const SegP*>& segs, const std::
   const int G = (int)ch.segs.size();
   for (int g = 0; g < G; ++g) {
     Ctx d = c;
-    d.wpart = c.scratch + p->wpart_off + (size_t)(g + 1) * p->wpart_stride;
+    d.wpart = c.scratch + p->wpart_chains + (size_t)g * p->wpart_stride;
     if (p->kpart_stride != 0) d.kpart = c.scratch + p->kpart_off + (size_t)(g + 1) * p->kpart_stride;
     if (p->act_stride != 0) d.act = c.scratch + p->act_off + (size_t)(g + 1) * p->act_stride;
     ch.ctx.push_back(d);
@@ -2056,16 +2056,18 @@ pnn_status pnn_plan_create(const pnn_net_desc* d, pnn_plan** out) {
       sv = align256(sv + s.saved_bytes);
     }
   p->saved_bytes = sv;
-  size_t wp = wgrad_level_bytes(p->fine, p->B, p->es);
-  wp = std::max(wp, wgrad_level_bytes(p->pre, p->B, p->es));
+  // (the chains run levels of fine segments; the coarse blocks' weight gradients of all levels at once, many times
+  // as large, only the calls' own region)
+  const size_t wf = align256(wgrad_level_bytes(p->fine, p->B, p->es));
+  size_t wp = std::max(wf, wgrad_level_bytes(p->pre, p->B, p->es));
   for (auto& s : p->coarse) wp = std::max(wp, wgrad_level_bytes(std::vector<SegP>{s}, p->B, p->es));
   wp = std::max(wp, wgrad_all_bytes(p->coarse, p->B, p->es));     // coarse_bwd_all
   wp = std::max(wp, wgrad_all_bytes(p->pre, p->B, p->es));        // pnn_pre_bwd, every level at once
   size_t sc = 0;
   p->wpart_off = sc;
-  p->wpart_bytes = wp;
-  p->wpart_stride = align256(wp);
-  sc = align256(sc + p->wpart_stride * (PNN_MAX_CHAINS + 1));
+  p->wpart_chains = align256(sc + wp);
+  p->wpart_stride = wf;
+  sc = p->wpart_chains + p->wpart_stride * PNN_MAX_CHAINS;
   p->kpart_off = sc;
   p->kpart_stride = plan_splits_k(p) ? GEMM_KPART_BYTES : 0;
   sc = align256(sc + p->kpart_stride * (PNN_MAX_CHAINS + 1));

@@ -188,3 +188,18 @@ def test_nonfinite_flag_words():
     assert L.pnn_flags_clear(p.handle, None, None) == -1
     assert L.pnn_flags_clear(None, 1 << 30, None) == -1
     p.close()
+
+
+def test_deferred_weight_gradients_are_counted_once():
+    """The partial sums of the coarse blocks' weight gradients, all levels at once, have a region in the call's own
+    scratch only: the fine sub-networks' chains hold a level of their own.  Wide blocks (0.7 GB of partial sums) may
+    add 1 GB to the plan of narrow ones; a copy per chain would add 3.6 GB."""
+    _lib_or_skip()
+    nets = [S.nets.resnet_parareal("scratch", 128, 32, 12, 10, "bf16", (1, 2, 3), coarse=c, units_per_stage=12)
+            for c in ("paper", "config")]
+    size = []
+    for net in nets:
+        p = B.Plan(net)
+        size.append(p.workspace_size(B.PNN_WS_SCRATCH))
+        p.close()
+    assert size[0] <= size[1] + (1 << 30), size
